@@ -34,9 +34,9 @@
  *     which case nothing was enqueued and outputs are untouched.  No C++
  *     exception crosses the ABI.  lsb_last_error() gives a message for the
  *     last failed call on the calling thread.
- *   - Any alignment is accepted.  The fast kernels need the cover and stego
- *     (or stego) pointers 16-byte aligned; otherwise a per-byte kernel runs
- *     (same results, lower bandwidth).
+ *   - Any alignment is accepted, by the same kernels: the GPU takes unaligned
+ *     global accesses of every width (buffers off a 4-byte boundary lose up
+ *     to a fifth of the bandwidth).
  *   - Threads: every call may be made from several host threads at once,
  *     except that one lsb_plan is used by one thread at a time (distinct
  *     plans are independent).  The shared state is the launch-configuration

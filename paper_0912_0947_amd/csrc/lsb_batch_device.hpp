@@ -87,14 +87,10 @@ __device__ __forceinline__ void run_tile(const DevJob &J, uint64_t v_begin, uint
     s.t0 = 0;
     s.k = J.k;
     s.hdr_len = 4;
-    s.words = 1;  // offsets are multiples of 256: stream side is dword aligned
     const bool raw = RAW && J.raw;
     if (raw) {
-        // stream byte 0 sits at a 256-byte aligned offset, so the stream side
-        // is dword aligned exactly when field t0 starts on a 32-bit boundary
         s.t0 = J.t0;
         s.hdr_len = 0;
-        s.words = (((uint64_t)J.k * J.t0) & 31u) == 0;
     }
     if constexpr (EMB) {
         if (!EXT || J.op == LSB_OP_EMBED) {

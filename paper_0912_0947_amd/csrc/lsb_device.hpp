@@ -14,7 +14,8 @@
 // stream bits = 2k whole stream bytes (16k is a multiple of 8, so when k*t0
 // is byte aligned every vector starts on a stream byte).  A lane moves one
 // 16-byte vector of cover/stego per step with a single dwordx4 access and the
-// matching 2k stream bytes with dword (k even) or short (k odd) accesses.
+// matching 2k stream bytes with dwords (and a short for odd k), all at any
+// byte address.
 // Vectors are grouped 64 per wave access so that every load and store
 // instruction of a wave touches one contiguous 1 KiB span.
 //
@@ -31,6 +32,16 @@
 namespace lsb {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// Memory forms of a vector, a dword and a short at any byte address: gfx950
+// takes unaligned global accesses of every width (the compiler emits the same
+// instructions as for aligned ones), so buffers need no alignment at all.
+// A 36 MB cover behind a 54-byte file header at k = 2 (embed, then extract):
+// 29 us, against 91 us through the per-byte kernels that misaligned buffers
+// used to take and 26 us aligned.  At 201 MB an offset of 6 bytes costs the
+// embed 3-10 % and the extract 10-20 %, an offset of 8 nothing.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
 
 __host__ __device__ inline uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
@@ -48,7 +59,6 @@ struct Span {
     uint32_t hdr_len;     // 4 in header mode, 0 in raw mode
     int k;
     int inplace;          // embed: dst == src, skip copy-only bytes
-    int words;            // stream side may use dword/short accesses
     int block_order;      // plain kernels: 1 = blocks in runs of 16 per XCD
 };
 
@@ -107,14 +117,14 @@ __host__ __device__ inline Ranges extract_ranges(const Span &s) {
 // Memory access helpers.
 template <bool NT>
 __device__ __forceinline__ u32x4 load16(const uint8_t *p) {
-    const u32x4 *q = reinterpret_cast<const u32x4 *>(p);
+    const u32x4_any *q = reinterpret_cast<const u32x4_any *>(p);
     if constexpr (NT) return __builtin_nontemporal_load(q);
     else return *q;
 }
 
 template <bool NT>
 __device__ __forceinline__ void store16(uint8_t *p, u32x4 v) {
-    u32x4 *q = reinterpret_cast<u32x4 *>(p);
+    u32x4_any *q = reinterpret_cast<u32x4_any *>(p);
     if constexpr (NT) __builtin_nontemporal_store(v, q);
     else *q = v;
 }
@@ -130,47 +140,33 @@ __device__ __forceinline__ uint32_t stream_byte(const Span &s, uint64_t i) {
 // Number of 32-bit words holding one vector's 16k stream bits.
 template <int K> struct Chunk { static constexpr int NW = (K + 1) / 2; };
 
-// Load one vector's 2K stream bytes that start at `p` as big-endian words
-// (bit 31 of w[0] is the vector's first stream bit).  `p` is 4-byte aligned
-// for even K, 2-byte aligned for odd K.
+// Load one vector's 2K stream bytes that start at `p` (any alignment) as
+// big-endian words (bit 31 of w[0] is the vector's first stream bit).
 template <int K>
-__device__ __forceinline__ void load_chunk_words(const uint8_t *p, uint32_t *w) {
-    if constexpr (K % 2 == 0) {
+__device__ __forceinline__ void load_chunk(const uint8_t *p, uint32_t *w) {
+    const u32_any *q = reinterpret_cast<const u32_any *>(p);
 #pragma unroll
-        for (int i = 0; i < K / 2; ++i)
-            w[i] = bswap32(reinterpret_cast<const uint32_t *>(p)[i]);
-    } else {
-        const uint16_t *h = reinterpret_cast<const uint16_t *>(p);
-#pragma unroll
-        for (int i = 0; i < K / 2; ++i)
-            w[i] = bswap32((uint32_t)h[2 * i] | ((uint32_t)h[2 * i + 1] << 16));
-        w[K / 2] = bswap32((uint32_t)h[K - 1]);
-    }
+    for (int i = 0; i < K / 2; ++i) w[i] = bswap32(q[i]);
+    if constexpr (K % 2 == 1) w[K / 2] = bswap32((uint32_t)*reinterpret_cast<const u16_any *>(p + 2 * K - 2));
 }
 
-// Same with byte accesses and a bit offset r in 0..7 (misaligned stream
-// pointer or k*t0 not byte aligned).  Reads 2K bytes, plus one if r > 0.
+// Same where the vector's first stream bit is bit r (1..7) of byte p[0]
+// (k*t0 not byte aligned): reads 2K + 1 bytes, all of which hold bits of the
+// vector.
 template <int K>
-__device__ __forceinline__ void load_chunk_bytes(const uint8_t *p, uint32_t r, uint32_t *w) {
-    constexpr int NB = 2 * K;
-    uint32_t b[NB + 1];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) b[i] = p[i];
-    b[NB] = r ? p[NB] : 0u;
-    uint32_t W[Chunk<K>::NW + 1];
-#pragma unroll
-    for (int i = 0; i <= Chunk<K>::NW; ++i) {
-        uint32_t v = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int idx = 4 * i + j;
-            v = (v << 8) | (idx <= NB ? b[idx] : 0u);
-        }
-        W[i] = v;
+__device__ __forceinline__ void load_chunk_shifted(const uint8_t *p, uint32_t r, uint32_t *w) {
+    constexpr int NW = Chunk<K>::NW;
+    uint32_t W[NW + 1];
+    load_chunk<K>(p, W);
+    const uint32_t last = p[2 * K];
+    if constexpr (K % 2 == 0) {
+        W[NW] = last << 24;
+    } else {
+        W[NW - 1] |= last << 8;
+        W[NW] = 0;
     }
 #pragma unroll
-    for (int i = 0; i < Chunk<K>::NW; ++i)
-        w[i] = r ? ((W[i] << r) | (W[i + 1] >> (32 - r))) : W[i];
+    for (int i = 0; i < NW; ++i) w[i] = (W[i] << r) | (W[i + 1] >> (32 - r));
 }
 
 // Field f (0..15) of a vector: K bits at chunk bit offset K*f.
@@ -254,27 +250,18 @@ __device__ __forceinline__ void extract_vec(u32x4 c, uint32_t *w) {
     }
 }
 
-// Store one vector's 2K stream bytes from big-endian words at `p` (4-byte
-// aligned for even K, 2-byte aligned for odd K).
+// Store one vector's 2K stream bytes from big-endian words at `p` (any
+// alignment).
 template <int K>
-__device__ __forceinline__ void store_chunk_words(uint8_t *p, const uint32_t *w) {
-    if constexpr (K % 2 == 0) {
+__device__ __forceinline__ void store_chunk(uint8_t *p, const uint32_t *w) {
+    u32_any *q = reinterpret_cast<u32_any *>(p);
 #pragma unroll
-        for (int i = 0; i < K / 2; ++i) reinterpret_cast<uint32_t *>(p)[i] = bswap32(w[i]);
-    } else {
-        uint16_t *h = reinterpret_cast<uint16_t *>(p);
-#pragma unroll
-        for (int i = 0; i < K / 2; ++i) {
-            const uint32_t le = bswap32(w[i]);
-            h[2 * i] = (uint16_t)le;
-            h[2 * i + 1] = (uint16_t)(le >> 16);
-        }
-        h[K - 1] = (uint16_t)bswap32(w[K / 2]);
-    }
+    for (int i = 0; i < K / 2; ++i) q[i] = bswap32(w[i]);
+    if constexpr (K % 2 == 1) *reinterpret_cast<u16_any *>(p + 2 * K - 2) = (uint16_t)bswap32(w[K / 2]);
 }
 
 // -------------------------------------------------------------------------
-// Per-byte forms used for edge vectors and for misaligned buffers.
+// Per-byte forms used for edge vectors.
 
 // Embed buffer byte t.  Writes nothing for a copy-only byte of an in-place span.
 // KC > 0 fixes k at compile time (as in the range functions); 0 reads s.k.
@@ -346,8 +333,8 @@ __device__ __forceinline__ void embed_walk(const Span &s, const Ranges &r, uint6
                 const uint64_t u = u0 + (uint64_t)j * 64 + lane;
                 c[j] = load16<NT>(s.src + 16 * u);
                 const uint8_t *p = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u);
-                if (s.words) load_chunk_words<K>(p, w[j]);
-                else load_chunk_bytes<K>(p, rbit, w[j]);
+                if (rbit == 0) load_chunk<K>(p, w[j]);
+                else load_chunk_shifted<K>(p, rbit, w[j]);
             }
 #pragma unroll
             for (int j = 0; j < UNR; ++j) {
@@ -371,8 +358,8 @@ __device__ __forceinline__ void embed_walk(const Span &s, const Ranges &r, uint6
                 if (u >= r.fast_begin && u < r.fast_end) {
                     uint32_t w[Chunk<K>::NW];
                     const uint8_t *p = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u);
-                    if (s.words) load_chunk_words<K>(p, w);
-                    else load_chunk_bytes<K>(p, rbit, w);
+                    if (rbit == 0) load_chunk<K>(p, w);
+                    else load_chunk_shifted<K>(p, rbit, w);
                     store16<NT>(s.dst + 16 * u, embed_vec<K>(load16<NT>(s.src + 16 * u), w));
                 } else if (u >= r.copy_begin && u < r.copy_end) {
                     if (!s.inplace) store16<NT>(s.dst + 16 * u, load16<NT>(s.src + 16 * u));
@@ -386,10 +373,7 @@ __device__ __forceinline__ void embed_walk(const Span &s, const Ranges &r, uint6
 }
 
 // Store the stream bytes of one fast wave group whose stego vectors are in c.
-// Every vector of the group is extracted before the first store, and the
-// stores sit in one branch on the stream side's width: with a branch per
-// vector, the wait inserted where the two store paths join made the wave
-// wait for each vector's store to complete before extracting the next.
+// Every vector of the group is extracted before the first store.
 template <int K, int UNR>
 __device__ __forceinline__ void extract_store_group(const Span &s, uintptr_t out_base, uint64_t u0,
                                                     const u32x4 *c, uint32_t lane) {
@@ -397,16 +381,8 @@ __device__ __forceinline__ void extract_store_group(const Span &s, uintptr_t out
 #pragma unroll
     for (int j = 0; j < UNR; ++j) extract_vec<K>(c[j], w[j]);
     uint8_t *p0 = reinterpret_cast<uint8_t *>(out_base + 2 * K * (u0 + lane));
-    if (s.words) {
 #pragma unroll
-        for (int j = 0; j < UNR; ++j) store_chunk_words<K>(p0 + 2 * K * 64 * j, w[j]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < UNR; ++j)
-#pragma unroll
-            for (int i = 0; i < 2 * K; ++i)
-                p0[2 * K * 64 * j + i] = (uint8_t)(w[j][i >> 2] >> (24 - 8 * (i & 3)));
-    }
+    for (int j = 0; j < UNR; ++j) store_chunk<K>(p0 + 2 * K * 64 * j, w[j]);
 }
 
 // Same for k = 1 with wavefront ballots.  The wave's 1 KiB of stego bytes
@@ -433,13 +409,8 @@ __device__ __forceinline__ void extract_store_group_ballot(const Span &s, uintpt
         if (lane < 16) {
             const uint64_t v = __builtin_bswap64(__builtin_bitreverse64(mine));
             uint8_t *p = reinterpret_cast<uint8_t *>(out_base + 2 * (u0 + (uint64_t)j * 64) + 8 * lane);
-            if (s.words) {
-                reinterpret_cast<uint32_t *>(p)[0] = (uint32_t)v;
-                reinterpret_cast<uint32_t *>(p)[1] = (uint32_t)(v >> 32);
-            } else {
-#pragma unroll
-                for (int b = 0; b < 8; ++b) p[b] = (uint8_t)(v >> (8 * b));
-            }
+            reinterpret_cast<u32_any *>(p)[0] = (uint32_t)v;
+            reinterpret_cast<u32_any *>(p)[1] = (uint32_t)(v >> 32);
         }
     }
 }
@@ -476,11 +447,7 @@ __device__ __forceinline__ void extract_walk(const Span &s, const Ranges &r, uin
                 if (u >= r.fast_begin && u < r.fast_end) {
                     uint32_t w[Chunk<K>::NW];
                     extract_vec<K>(load16<NT>(s.src + 16 * u), w);
-                    if (s.words) {
-                        store_chunk_words<K>(p, w);
-                    } else {
-                        for (int i = 0; i < 2 * K; ++i) p[i] = (uint8_t)(w[i >> 2] >> (24 - 8 * (i & 3)));
-                    }
+                    store_chunk<K>(p, w);
                 } else {
                     const uint64_t i0 = sb + 2 * K * u;
                     const uint64_t end_byte = ceil_div(s.bits, 8);

@@ -131,42 +131,6 @@ __global__ void __launch_bounds__(1024)
     extract_walk<K, UNR, NT, BALLOT>(s, r, v_begin, r.count, wave, n_waves, lane, stage);
 }
 
-// Per-byte embed for buffers whose cover or stego pointer is not 16-byte
-// aligned: one buffer byte per thread step.
-__global__ void __launch_bounds__(256) lsb_embed_bytes_kernel(Span s, uint64_t count) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count; t += stride)
-        embed_byte(s, t);
-}
-
-// Per-byte extract for a misaligned stego pointer: one output stream byte
-// per thread step.
-__global__ void __launch_bounds__(256)
-    lsb_extract_bytes_kernel(Span s, int header, uint64_t out_cap, uint32_t *len_out, int32_t *status_out) {
-    const uint32_t lane = threadIdx.x & 63u;
-    if (header) {
-        uint32_t len = 0;
-        int status = LSB_E_HEADER;
-        if ((uint64_t)s.k * s.n >= 32) {
-            len = decode_header(s.src, s.k, lane);
-            if (4 + (uint64_t)len > room_bytes(s.n, s.k)) status = LSB_E_HEADER;
-            else if ((uint64_t)len > out_cap) status = LSB_E_BUFFER;
-            else status = LSB_OK;
-        }
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            *len_out = len;
-            *status_out = status;
-        }
-        if (status != LSB_OK) return;
-        s.bits = 8 * (4 + (uint64_t)len);
-    }
-    const uint64_t first = stream_byte0(s) > s.hdr_len ? stream_byte0(s) : s.hdr_len;
-    const uint64_t end = ceil_div(s.bits, 8);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = first + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < end; i += stride)
-        s.out[i - s.hdr_len] = (uint8_t)extract_stream_byte(s, i);
-}
-
 // ---------------------------------------------------------------------------
 // Dispatch tables: [k-1][unroll index][nontemporal].
 typedef void (*EmbedFn)(Span);
@@ -221,43 +185,15 @@ static ExtractFn extract_fn(int k, int u, int nt, int pack) {
     }
 }
 
-static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
-
-// Stream-side accesses may use dword (even k) / short (odd k) width when the
-// address of the first stream byte of vector 0 is 4-byte aligned and k*t0 is
-// byte aligned.
-static int stream_words(const void *base, uint32_t hdr_len, const Span &s) {
-    if (((uint64_t)s.k * s.t0) & 7) return 0;
-    const uintptr_t a = (uintptr_t)base - hdr_len + stream_byte0(s);
-    return (a & 3u) == 0;
-}
-
 int launch_embed(const Span &s0, const lsb_launch_cfg &c, hipStream_t stream) {
     Span s = s0;
-    s.words = stream_words(s.body, s.hdr_len, s);
     s.block_order = c.order;
-    if (!aligned16(s.src) || !aligned16(s.dst)) {
-        // per-byte kernel over the bytes that must be written
-        uint64_t count = s.n;
-        if (s.inplace) {
-            const uint64_t any = ceil_div(s.bits, (uint64_t)s.k);
-            count = any > s.t0 ? any - s.t0 : 0;
-            if (count > s.n) count = s.n;
-        }
-        if (!count) return LSB_OK;
-        uint64_t blocks = ceil_div(count, 256);
-        if (blocks > 65536) blocks = 65536;
-        hipEvent_t e0, e1;
-        take_launch_events(&e0, &e1);
-        hipExtLaunchKernelGGL(lsb_embed_bytes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, e0, e1, 0, s, count);
-    } else {
-        const Ranges r = embed_ranges(s);
-        if (!r.count) return LSB_OK;
-        EmbedFn fn = embed_fn(s.k, c.unroll, c.nontemporal);
-        hipEvent_t e0, e1;
-        take_launch_events(&e0, &e1);
-        hipExtLaunchKernelGGL(fn, dim3(grid_for(c, r.count)), dim3(c.block), 0, stream, e0, e1, 0, s);
-    }
+    const Ranges r = embed_ranges(s);
+    if (!r.count) return LSB_OK;
+    EmbedFn fn = embed_fn(s.k, c.unroll, c.nontemporal);
+    hipEvent_t e0, e1;
+    take_launch_events(&e0, &e1);
+    hipExtLaunchKernelGGL(fn, dim3(grid_for(c, r.count)), dim3(c.block), 0, stream, e0, e1, 0, s);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? LSB_OK : hip_fail(e, "embed kernel launch");
 }
@@ -265,23 +201,12 @@ int launch_embed(const Span &s0, const lsb_launch_cfg &c, hipStream_t stream) {
 int launch_extract(const Span &s0, int header, uint64_t out_cap, uint32_t *len_out, int32_t *status_out,
                    uint64_t max_vectors, const lsb_launch_cfg &c, hipStream_t stream) {
     Span s = s0;
-    s.words = stream_words(s.out, s.hdr_len, s);
     s.block_order = c.order;
-    if (!aligned16(s.src)) {
-        uint64_t bytes = max_vectors * 2 * (uint64_t)s.k;  // output stream bytes bound
-        uint64_t blocks = ceil_div(bytes ? bytes : 1, 256);
-        if (blocks > 65536) blocks = 65536;
-        hipEvent_t e0, e1;
-        take_launch_events(&e0, &e1);
-        hipExtLaunchKernelGGL(lsb_extract_bytes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, e0, e1, 0, s,
-                              header, out_cap, len_out, status_out);
-    } else {
-        ExtractFn fn = extract_fn(s.k, c.unroll, c.nontemporal, c.pack);
-        hipEvent_t e0, e1;
-        take_launch_events(&e0, &e1);
-        hipExtLaunchKernelGGL(fn, dim3(grid_for(c, max_vectors)), dim3(c.block), 0, stream, e0, e1, 0, s, header,
-                              out_cap, len_out, status_out);
-    }
+    ExtractFn fn = extract_fn(s.k, c.unroll, c.nontemporal, c.pack);
+    hipEvent_t e0, e1;
+    take_launch_events(&e0, &e1);
+    hipExtLaunchKernelGGL(fn, dim3(grid_for(c, max_vectors)), dim3(c.block), 0, stream, e0, e1, 0, s, header, out_cap,
+                          len_out, status_out);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? LSB_OK : hip_fail(e, "extract kernel launch");
 }

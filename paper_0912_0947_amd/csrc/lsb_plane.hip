@@ -32,21 +32,17 @@ __device__ __forceinline__ uint32_t sq_diff4(uint32_t a, uint32_t b) {
 }
 
 // Sum of squared byte differences; one 64-bit atomic per wave.
-__global__ void __launch_bounds__(256) lsb_sse_kernel(const uint8_t *a, const uint8_t *b, uint64_t n, int vec,
+__global__ void __launch_bounds__(256) lsb_sse_kernel(const uint8_t *a, const uint8_t *b, uint64_t n,
                                                      unsigned long long *out) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t acc = 0;
-    uint64_t tail = 0;
-    if (vec) {
-        const uint64_t nv = n / 16;
-        for (uint64_t u = gid; u < nv; u += stride) {
-            const u32x4 x = load16<true>(a + 16 * u), y = load16<true>(b + 16 * u);
-            acc += sq_diff4(x[0], y[0]) + sq_diff4(x[1], y[1]) + sq_diff4(x[2], y[2]) + sq_diff4(x[3], y[3]);
-        }
-        tail = 16 * nv;
+    const uint64_t nv = n / 16;
+    for (uint64_t u = gid; u < nv; u += stride) {
+        const u32x4 x = load16<true>(a + 16 * u), y = load16<true>(b + 16 * u);
+        acc += sq_diff4(x[0], y[0]) + sq_diff4(x[1], y[1]) + sq_diff4(x[2], y[2]) + sq_diff4(x[3], y[3]);
     }
-    for (uint64_t t = tail + gid; t < n; t += stride) {
+    for (uint64_t t = 16 * nv + gid; t < n; t += stride) {
         const int d = (int)a[t] - (int)b[t];
         acc += (uint64_t)(d * d);
     }
@@ -138,9 +134,8 @@ int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels, uint3
         return fail(LSB_E_ARG, "lsb_embed_plane: cover and stego overlap (only stego == cover is allowed)");
     if (overlaps(msg, len, stego, n)) return fail(LSB_E_ARG, "lsb_embed_plane: msg overlaps stego");
     hipStream_t st = (hipStream_t)stream;
-    const bool aligned = (((uintptr_t)cover | (uintptr_t)stego) & 15u) == 0;
     if (c == 1) return lsb_embed(cover, stego, pixels, msg, len, k, stream);  // the plane is the image
-    if (aligned && c <= 4) {
+    if (c <= 4) {
         // one pass: each lane moves 16 pixels (c vectors) and rewrites their plane bytes
         Span s{};
         s.src = cover;
@@ -152,7 +147,6 @@ int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels, uint3
         s.hdr_len = 4;
         s.k = k;
         s.inplace = cover == stego;
-        s.words = (((uintptr_t)msg - 4) & 3u) == 0;
         const Ranges r = embed_ranges(s);
         if (!r.count) return LSB_OK;
         hipEvent_t e0, e1;
@@ -161,11 +155,9 @@ int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels, uint3
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? LSB_OK : hip_fail(e, "plane embed kernel launch");
     }
-    // other channel counts or misaligned buffers: copy, then rewrite the plane bytes
-    if (cover != stego) {
-        const int vec = aligned;
-        hipLaunchKernelGGL(lsb_copy_kernel, dim3(grid_cap(vec ? n / 16 : n)), dim3(256), 0, st, cover, stego, n, vec);
-    }
+    // other channel counts: copy, then rewrite the plane bytes
+    if (cover != stego)
+        hipLaunchKernelGGL(lsb_copy_kernel, dim3(grid_cap(n / 16)), dim3(256), 0, st, cover, stego, n);
     Span s{};
     s.src = stego;  // after the copy the plane bytes are read back from stego
     s.dst = stego;
@@ -211,8 +203,7 @@ int lsb_extract_plane(const uint8_t *stego, uint64_t pixels, uint32_t c, uint32_
     s.k = k;
     hipEvent_t e0, e1;
     take_launch_events(&e0, &e1);
-    if (c <= 4 && ((uintptr_t)stego & 15u) == 0) {
-        s.words = (((uintptr_t)msg_out - 4) & 3u) == 0;
+    if (c <= 4) {
         uint64_t vectors = 0;  // bound on the vectors a decodable stream can need
         if ((uint64_t)k * pixels >= 32) {
             const uint64_t v_stream = ceil_div(4 + max_len, 2 * (uint64_t)k);
@@ -237,13 +228,12 @@ int lsb_sse(const uint8_t *a, const uint8_t *b, uint64_t n, uint64_t *sse_dev, v
         return fail(LSB_E_ARG, "lsb_sse: result overlaps an input");
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(lsb_zero_u64_kernel, dim3(1), dim3(1), 0, st, sse_dev);
-    const int vec = (((uintptr_t)a | (uintptr_t)b) & 15u) == 0;
     hipEvent_t e0, e1;
     take_launch_events(&e0, &e1);
-    uint64_t blocks = ceil_div((vec ? n / 16 : n) + 1, 256);
+    uint64_t blocks = ceil_div(n / 16 + 1, 256);
     const uint64_t cap = (uint64_t)device_cus() * 4;  // few atomics on the one result word
     if (blocks > cap) blocks = cap;
-    hipExtLaunchKernelGGL(lsb_sse_kernel, dim3((unsigned)blocks), dim3(256), 0, st, e0, e1, 0, a, b, n, vec,
+    hipExtLaunchKernelGGL(lsb_sse_kernel, dim3((unsigned)blocks), dim3(256), 0, st, e0, e1, 0, a, b, n,
                           (unsigned long long *)sse_dev);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? LSB_OK : hip_fail(e, "sse kernel launch");

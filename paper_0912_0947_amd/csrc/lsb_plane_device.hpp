@@ -50,16 +50,12 @@ __device__ __forceinline__ uint32_t plane_stream_byte(const Span &s, uint64_t i,
     return v & ((0xFF00u >> valid) & 0xFFu);
 }
 
-__global__ void __launch_bounds__(256) lsb_copy_kernel(const uint8_t *src, uint8_t *dst, uint64_t n, int vec) {
+__global__ void __launch_bounds__(256) lsb_copy_kernel(const uint8_t *src, uint8_t *dst, uint64_t n) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (vec) {
-        const uint64_t nv = n / 16;
-        for (uint64_t u = gid; u < nv; u += stride) store16<true>(dst + 16 * u, load16<true>(src + 16 * u));
-        for (uint64_t t = 16 * nv + gid; t < n; t += stride) dst[t] = src[t];
-    } else {
-        for (uint64_t t = gid; t < n; t += stride) dst[t] = src[t];
-    }
+    const uint64_t nv = n / 16;
+    for (uint64_t u = gid; u < nv; u += stride) store16<true>(dst + 16 * u, load16<true>(src + 16 * u));
+    for (uint64_t t = 16 * nv + gid; t < n; t += stride) dst[t] = src[t];
 }
 
 __global__ void __launch_bounds__(256) lsb_plane_embed_kernel(Span s, uint64_t fields, uint32_t c, uint32_t plane) {
@@ -181,8 +177,7 @@ __device__ __forceinline__ void plane_group_embed(const Span &s, u32x4 *stage, u
     for (int i = 0; i < C; ++i) v[i] = stage[C * lane + i];
     uint32_t w[Chunk<K>::NW];
     const uint8_t *p = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u);
-    if (s.words) load_chunk_words<K>(p, w);
-    else load_chunk_bytes<K>(p, 0, w);
+    load_chunk<K>(p, w);
     plane_embed_vec_any<K, C>(v, w, plane);
 #pragma unroll
     for (int i = 0; i < C; ++i) stage[C * lane + i] = v[i];
@@ -200,8 +195,7 @@ __device__ __forceinline__ void plane_embed_unit(const Span &s, const Ranges &r,
         for (int i = 0; i < C; ++i) v[i] = load16<true>(src + 16 * i);
         uint32_t w[Chunk<K>::NW];
         const uint8_t *p = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u);
-        if (s.words) load_chunk_words<K>(p, w);
-        else load_chunk_bytes<K>(p, 0, w);
+        load_chunk<K>(p, w);
         plane_embed_vec_any<K, C>(v, w, plane);
 #pragma unroll
         for (int i = 0; i < C; ++i) store16<true>(dst + 16 * i, v[i]);
@@ -236,7 +230,7 @@ __device__ __forceinline__ int plane_group_class(const Ranges &r, uint64_t u0) {
 }
 
 // Embed over the plane view; s.n = pixels, s.src/s.dst the interleaved
-// cover/stego (16-byte aligned), header mode (t0 = 0).
+// cover/stego, header mode (t0 = 0).
 template <int K, int C>
 __global__ void __launch_bounds__(256) lsb_plane_embed_vec_kernel(Span s, uint32_t plane) {
     __shared__ u32x4 stage_all[4][64 * C];  // one stage per wave of the 256-thread block
@@ -275,12 +269,7 @@ __device__ __forceinline__ void plane_extract_vec_out(const Span &s, const u32x4
     uint32_t w[Chunk<K>::NW];
     extract_vec<K>(plane_gather_any<K, C>(v, plane), w);
     uint8_t *p = reinterpret_cast<uint8_t *>(out_base + 2 * K * u);
-    if (s.words) {
-        store_chunk_words<K>(p, w);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 2 * K; ++i) p[i] = (uint8_t)(w[i >> 2] >> (24 - 8 * (i & 3)));
-    }
+    store_chunk<K>(p, w);
 }
 
 template <int K, int C>

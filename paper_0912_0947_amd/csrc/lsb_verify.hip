@@ -120,8 +120,7 @@ __device__ __forceinline__ uint32_t verify_one(const Span &s, const Ranges &r, u
     if (u >= r.fast_begin && u < r.fast_end) {
         uint32_t w[Chunk<K>::NW];
         const uint8_t *p = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u);
-        if (s.words) load_chunk_words<K>(p, w);
-        else load_chunk_bytes<K>(p, 0, w);
+        load_chunk<K>(p, w);
         return vec_wrong<K>(load16<true>(s.src + 16 * u), load16<true>(s.dst + 16 * u), w);
     }
     if (u >= r.copy_begin && u < r.copy_end)
@@ -146,13 +145,8 @@ __global__ void __launch_bounds__(256) lsb_verify_kernel(Span s, unsigned long l
             uint32_t w0[Chunk<K>::NW], w1[Chunk<K>::NW];
             const uint8_t *p0 = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u0);
             const uint8_t *p1 = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u1);
-            if (s.words) {
-                load_chunk_words<K>(p0, w0);
-                load_chunk_words<K>(p1, w1);
-            } else {
-                load_chunk_bytes<K>(p0, 0, w0);
-                load_chunk_bytes<K>(p1, 0, w1);
-            }
+            load_chunk<K>(p0, w0);
+            load_chunk<K>(p1, w1);
             const u32x4 c0 = load16<true>(s.src + 16 * u0), g0 = load16<true>(s.dst + 16 * u0);
             const u32x4 c1 = load16<true>(s.src + 16 * u1), g1 = load16<true>(s.dst + 16 * u1);
             bad += vec_wrong<K>(c0, g0, w0) + vec_wrong<K>(c1, g1, w1);
@@ -174,8 +168,7 @@ __device__ __forceinline__ uint32_t embed_verify_one(const Span &s, const Ranges
     if (u >= r.fast_begin && u < r.fast_end) {
         uint32_t w[Chunk<K>::NW];
         const uint8_t *p = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u);
-        if (s.words) load_chunk_words<K>(p, w);
-        else load_chunk_bytes<K>(p, 0, w);
+        load_chunk<K>(p, w);
         const u32x4 c = load16<true>(s.src + 16 * u);
         const u32x4 g = embed_vec<K>(c, w);
         store16<true>(s.dst + 16 * u, g);
@@ -212,13 +205,8 @@ __global__ void __launch_bounds__(256) lsb_embed_verify_kernel(Span s, unsigned 
             uint32_t w0[Chunk<K>::NW], w1[Chunk<K>::NW];
             const uint8_t *p0 = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u0);
             const uint8_t *p1 = reinterpret_cast<const uint8_t *>(body_base + 2 * K * u1);
-            if (s.words) {
-                load_chunk_words<K>(p0, w0);
-                load_chunk_words<K>(p1, w1);
-            } else {
-                load_chunk_bytes<K>(p0, 0, w0);
-                load_chunk_bytes<K>(p1, 0, w1);
-            }
+            load_chunk<K>(p0, w0);
+            load_chunk<K>(p1, w1);
             const u32x4 c0 = load16<true>(s.src + 16 * u0);
             const u32x4 c1 = load16<true>(s.src + 16 * u1);
             const u32x4 g0 = embed_vec<K>(c0, w0);
@@ -230,27 +218,6 @@ __global__ void __launch_bounds__(256) lsb_embed_verify_kernel(Span s, unsigned 
             bad += embed_verify_one<K>(s, r, body_base, u0);
             if (u1 < r.count) bad += embed_verify_one<K>(s, r, body_base, u1);
         }
-    }
-    add_block_count(bad, mismatches);
-}
-
-// Per-byte forms for buffers whose cover or stego pointer is not 16-byte
-// aligned.
-__global__ void __launch_bounds__(256) lsb_verify_bytes_kernel(Span s, unsigned long long *mismatches) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    uint32_t bad = 0;
-    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < s.n; t += stride)
-        bad += byte_wrong(s, t, s.src[t], s.dst[t]);
-    add_block_count(bad, mismatches);
-}
-
-__global__ void __launch_bounds__(256) lsb_embed_verify_bytes_kernel(Span s, unsigned long long *mismatches) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    uint32_t bad = 0;
-    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < s.n; t += stride) {
-        const uint32_t c = s.src[t];
-        embed_byte(s, t);
-        bad += byte_wrong(s, t, c, s.dst[t]);
     }
     add_block_count(bad, mismatches);
 }
@@ -312,24 +279,21 @@ static int verify_call(const char *name, bool embed, const uint8_t *cover, uint8
     s.hdr_len = 4;
     s.k = k;
     s.inplace = embed && cover == stego;
-    s.words = (((uintptr_t)msg - 4) & 3u) == 0;
     hipStream_t st = (hipStream_t)stream;
     unsigned long long *cnt = (unsigned long long *)mismatches_dev;
     hipLaunchKernelGGL(lsb_verify_zero_kernel, dim3(1), dim3(1), 0, st, cnt);
-    const bool vec = (((uintptr_t)cover | (uintptr_t)stego) & 15u) == 0;
-    uint64_t items = vec ? ceil_div(n, 16) : n;
-    if (vec && s.inplace) items = embed_ranges(s).count;  // in place: bytes past the stream stay untouched
-    // The vector kernels' blocks cover 512 vectors per pass, and the grid
+    uint64_t items = ceil_div(n, 16);
+    if (s.inplace) items = embed_ranges(s).count;  // in place: bytes past the stream stay untouched
+    // The kernels' blocks cover 512 vectors per pass, and the grid
     // gives every pair of vectors a thread: on a grid capped at 8 blocks
     // per CU the waves loop, and a looping wave's wait for its next loads
     // also waits for its previous stores (one counter covers both).  The
     // capped grid measured slower for the check alone too.  A correct
     // embedding adds nothing to the counter, so the larger grid costs no
     // atomics.
-    uint64_t blocks = ceil_div(items ? items : 1, vec ? 512 : 256);
+    uint64_t blocks = ceil_div(items ? items : 1, 512);
     if (blocks > (uint64_t)INT32_MAX) blocks = (uint64_t)INT32_MAX;
-    VerifyFn fn = vec ? (embed ? fn_for_k<EmbedVerifyK>(k) : fn_for_k<VerifyK>(k))
-                      : (embed ? lsb_embed_verify_bytes_kernel : lsb_verify_bytes_kernel);
+    VerifyFn fn = embed ? fn_for_k<EmbedVerifyK>(k) : fn_for_k<VerifyK>(k);
     hipEvent_t e0, e1;
     take_launch_events(&e0, &e1);
     hipExtLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(256), 0, st, e0, e1, 0, s, cnt);

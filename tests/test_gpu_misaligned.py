@@ -1,0 +1,50 @@
+"""Buffers at every byte offset 0..15 from an aligned allocation: whole wave
+groups of the vector kernels (and their edges) with unaligned cover, stego
+and message accesses, against the oracle byte for byte."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_0912_0947_amd import api, inputs
+
+from gpu_helpers import assert_bytes_equal, empty_dev, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k", range(1, 9))
+@pytest.mark.parametrize("off", range(16))
+def test_every_offset(k, off):
+    n = 70000 + off  # several groups of 64..256 vectors, a ragged tail
+    cover = inputs.random_bytes(n, 2701, k, off)
+    msg = inputs.random_bytes(oracle.capacity(n, k) - off, 2702, k, off)
+    rc, want = oracle.embed(cover, msg, k)
+    assert rc == oracle.OK
+    c, m = to_dev(cover, pad_before=off, pad_after=16), to_dev(msg, pad_before=15 - off, pad_after=16)
+    stego = empty_dev(n, pad_before=(7 * off) % 16)
+    api.embed(c, m, k, out=stego)
+    assert_bytes_equal(to_host(stego), want, "embed k=%d off=%d" % (k, off))
+    out, ls = api.extract(stego, k, out=empty_dev(msg.size, pad_before=(3 * off) % 16))
+    assert ls.cpu().tolist() == [msg.size, oracle.OK]
+    assert_bytes_equal(to_host(out), msg, "extract k=%d off=%d" % (k, off))
+    assert int(api.verify(c, stego, m, k).item()) == 0
+    stego.add_(16)  # bits above the field (k < 5) or in it: every byte differs from the embedding
+    assert int(api.verify(c, stego, m, k).item()) == n
+
+
+@pytest.mark.parametrize("c", [3, 4])
+@pytest.mark.parametrize("off", [1, 2, 6, 13])
+def test_plane_offsets(c, off):
+    pixels, k, plane = 9001, 2, c - 1
+    cover = inputs.random_bytes(pixels * c, 2703, c, off)
+    msg = inputs.random_bytes(oracle.capacity(pixels, k) - off, 2704, c, off)
+    rc, want = oracle.embed_plane(cover, c, plane, msg, k)
+    assert rc == oracle.OK
+    stego = empty_dev(cover.size, pad_before=off)
+    api.embed_plane(to_dev(cover, pad_before=off, pad_after=16), c, plane, to_dev(msg), k, out=stego)
+    assert_bytes_equal(to_host(stego), want, "plane embed c=%d off=%d" % (c, off))
+    out, ls = api.extract_plane(stego, c, plane, k, out=empty_dev(msg.size, pad_before=off))
+    assert ls.cpu().tolist() == [msg.size, oracle.OK]
+    assert_bytes_equal(to_host(out), msg, "plane extract c=%d off=%d" % (c, off))
+    assert int(api.sse(to_dev(cover, pad_before=off, pad_after=16), stego).item()) == int(
+        ((want.astype(np.int64) - cover) ** 2).sum())
