@@ -224,7 +224,7 @@ int lsb_embed_verify(const uint8_t *cover, uint8_t *stego, uint64_t n,
                      uint64_t *mismatches_dev, void *stream);
 
 /* ------------------------------------------------------------------------
- * Batched form: thousands of covers of uneven size and k in one persistent
+ * Batched form: thousands of covers of uneven size and k in one
  * launch (the paper's per-row loop over an image, Section VI steps 4-5, and
  * its frame loop over a video, generalised to independent covers).
  *
@@ -265,7 +265,7 @@ typedef struct lsb_plan lsb_plan;
  * pinned host memory (this is the only allocating call of the batched form).
  * A run is an asynchronous upload of the job table from the plan's pinned
  * mirror (only when the table changed since the last upload), then one
- * persistent kernel launch.
+ * kernel launch with a block per tile.
  *   jobs_host  host array of n_jobs jobs, or NULL to reserve room for n_jobs
  *              jobs and set them later with lsb_plan_update.
  *   op         LSB_OP_EMBED or LSB_OP_EXTRACT: every job of the plan is of
@@ -283,7 +283,7 @@ int lsb_plan_create(lsb_plan **plan, const lsb_job *jobs_host, int n_jobs, int o
 int lsb_plan_update(lsb_plan *plan, const lsb_job *jobs_host, int n_jobs);
 
 /* Run every job of the plan on `stream`.  Every run of a plan uses the
- * plan's device job table and tile counter: a run on another stream than
+ * plan's device job table: a run on another stream than
  * the plan's previous run first makes `stream` wait for that run.  The job
  * table is uploaded again only after lsb_plan_update.
  * For job j: status_dev[j] <- LSB_OK
@@ -329,11 +329,11 @@ int lsb_job_extents(const lsb_job *jobs, int n_jobs, int op,
 
 /* For callers that cannot allocate (serving loops and harnesses that may not
  * call hipMalloc): lsb_plan_create + lsb_plan_run in one call that allocates
- * nothing.  The job table and its tile counter go into a
+ * nothing.  The job table goes into a
  * fixed device array of the library (one per device, about 256 KiB, held
  * until the process ends) instead of plan memory; the table is staged in a
  * library host buffer and uploaded with an asynchronous copy on `stream`,
- * then the persistent kernel is launched on `stream` (no graph).  Jobs, arenas, len_dev and status_dev mean what they mean for
+ * then the batched kernel is launched on `stream` (no graph).  Jobs, arenas, len_dev and status_dev mean what they mean for
  * lsb_plan_create(op) + lsb_plan_run, and the results are identical.
  * At most LSB_STATIC_MAX_JOBS jobs: more is LSB_E_ARG (use a plan).  Every
  * call on one device shares that device's table: calls on one stream run in
@@ -386,10 +386,10 @@ int lsb_autotune(int op, int k, uint64_t n, uint8_t *cover, uint8_t *stego,
 
 /* Batched-kernel configuration: tile size in 16-byte vectors per embed tile
  * (extract tiles span twice as many; a multiple of 64 in [64, 2^30]), the
- * kernel's block/unroll/nontemporal choice and its grid cap.  Blocks need at
- * least 128 threads: one wave of each block hands out the tiles that the
- * others stream.  Plans read the tile size at lsb_plan_update and the rest
- * at each run. */
+ * kernel's block/unroll/nontemporal choice and its grid cap (0: a block per
+ * tile; a capped grid walks the tiles with a stride).  Blocks need at least
+ * 128 threads.  Plans read the tile size at lsb_plan_update and the rest at
+ * each run. */
 int lsb_batch_tune_get(lsb_launch_cfg *cfg, int64_t *tile_vectors);
 int lsb_batch_tune_set(const lsb_launch_cfg *cfg, int64_t tile_vectors);
 

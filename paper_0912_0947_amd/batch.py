@@ -1,4 +1,4 @@
-"""Batched embed/extract: many covers of uneven size and k in one persistent
+"""Batched embed/extract: many covers of uneven size and k in one
 launch (lsb_plan_* in include/lsb.h).  Marshalling only."""
 from __future__ import annotations
 
@@ -66,7 +66,7 @@ _WORD = (torch.int32, torch.uint32) if hasattr(torch, "uint32") else (torch.int3
 
 class Plan:
     """Owns an lsb_plan: a device job table and its pinned host mirror (a
-    run uploads the table when it changed, then launches the persistent
+    run uploads the table when it changed, then launches the batched
     kernel).  Before each run
     the binding checks that the arenas hold every byte the jobs name and
     that the status and length arrays have an entry per job (the C call

@@ -1,28 +1,24 @@
 // lsb_batch.hip -- batched embed/extract over thousands of covers of uneven
-// size and k in one persistent launch.
+// size and k in one launch.
 //
 // The paper loops on the host over the rows of an image (Section VI steps
 // 4-5 split the data across rows; Section VII steps 3-4 likewise), paying a
 // copy and a launch per row.  Here every cover of a batch is a job, each job
-// is cut into tiles of T 16-byte vectors (2T for extract jobs), and one
-// persistent grid walks the global tile list, each block taking the next
-// tile from a counter.  Tile t of a job starts 16*T*t fields after the job's
-// first field, a whole number of stream bytes, so no two tiles of a job share
-// an output byte.  A job is a whole cover with its length header or a raw
-// slice [t0, t0 + n) of a longer logical cover; slices of one stream may be
-// spread over many jobs (the frames of a clip).
+// is cut into tiles of T 16-byte vectors (2T for extract jobs), and one launch
+// has a block per tile, which finds its job through a map from tiles to jobs.  Tile t of a job starts 16*T*t fields after the job's first field, a
+// whole number of stream bytes, so no two tiles of a job share an output
+// byte.  A job is a whole cover with its length header or a raw slice
+// [t0, t0 + n) of a longer logical cover; slices of one stream may be spread
+// over many jobs (the frames of a clip).
 //
 // One run: an asynchronous copy of the job table from the plan's pinned
 // host mirror, only when the table changed since the last upload, then the
-// persistent kernel.  The kernel also reports each job's status (and, for
-// extract jobs, the decoded length), and its last block resets the tile
-// counter, so a run whose table is already on the device is one kernel
-// launch.  (While a prologue kernel ran before the persistent one, the run
-// was a HIP graph of three nodes; with one kernel left, launching the graph
-// cost about 25 us more host time per run than launching the kernel.)
+// kernel, which also reports each job's status (and, for extract jobs, the
+// decoded length).  Nothing on the device changes between runs but outputs.
 #include <stddef.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 
@@ -37,10 +33,12 @@ static BatchFn batch_fn(int unroll, int nt, int cls, bool raw) {
 
 // Batched-kernel configuration (global, read at each run): the launch shape
 // of plans with embed jobs (entry 0) and of extract-only plans (entry 1),
-// and the tile size of both.
+// and the tile size of both.  A block walks its tile in one or two steps:
+// smaller tiles spend more blocks on the job lookup (two dependent scalar loads),
+// larger ones leave small covers with few blocks.
 static std::mutex g_batch_mu;
-static lsb_launch_cfg g_batch_cfg[2] = {{1024, 2, 2, 1, 0}, {1024, 4, 2, 1, 0}};
-static int64_t g_tile_vectors = 4096;
+static lsb_launch_cfg g_batch_cfg[2] = {{256, 2, 0, 1, 0}, {256, 4, 0, 1, 0}};
+static int64_t g_tile_vectors = 512;
 
 // Launch shape of a plan: extract-only plans have their own entry.
 static lsb_launch_cfg batch_cfg_for(bool has_embed, bool has_extract, int64_t *tv) {
@@ -53,18 +51,24 @@ static lsb_launch_cfg batch_cfg_for(bool has_embed, bool has_extract, int64_t *t
 
 using namespace lsb;
 
+// What a filled job table holds, for the launch.
+struct TableInfo {
+    uint64_t tiles = 0;
+    bool has_extract = false, has_embed = false;
+    bool has_raw = false;    // some job is a raw slice: the raw-capable kernels run
+    bool has_empty = false;  // some job has no tile: the kernel sweeps the table for them
+    int cls = 0;             // 1 + 8*op + (k-1) when every job shares (op, k); kCls*AnyK; else 0
+    int map_shift = 0;
+    size_t used_bytes = 0;   // records, first tile ids and the map's used entries
+};
+
 struct lsb_plan {
     int device = -1;
     int max_jobs = 0;
     int n_jobs = 0;
     int op_mode = LSB_OP_MIXED;  // LSB_OP_EMBED / LSB_OP_EXTRACT: every job of that kind
-    bool has_extract = false;
-    bool has_embed = false;
-    bool has_raw = false;  // some job is a raw slice: the raw-capable kernels run
-    int cls = 0;  // 1 + 8*op + (k-1) when every job shares (op, k); kClsExtractAnyK; else 0
-    uint64_t total_tiles = 0;
-    size_t table_bytes = 0;  // bytes of header + (max_jobs + 1) records
-    size_t used_bytes = 0;   // bytes the next upload copies
+    TableInfo info;          // what the host table holds
+    size_t table_bytes = 0;  // bytes of a full table of max_jobs jobs
     uint8_t *host = nullptr;  // pinned mirror of the device table
     uint8_t *dev = nullptr;
     hipEvent_t done = nullptr;  // recorded after each run
@@ -75,12 +79,12 @@ struct lsb_plan {
 };
 
 // ---------------------------------------------------------------------------
-// Table of lsb_batch_run_static: the job table and tile counter live in this
+// Table of lsb_batch_run_static: the job table lives in this
 // file-scope device array (one copy per device, held until the process
 // ends) instead of plan memory.  Host code never uses the array's name as an
 // address: static_table() looks up each device's copy once, with that
 // device current, and the launches take that pointer.
-constexpr size_t kStaticTableBytes = sizeof(PlanHeader) + sizeof(DevJob) * ((size_t)LSB_STATIC_MAX_JOBS + 1);
+constexpr size_t kStaticTableBytes = (size_t)table_layout(LSB_STATIC_MAX_JOBS).bytes;
 static __device__ __align__(256) uint8_t scratch[kStaticTableBytes];
 
 constexpr int kMaxDevices = 64;
@@ -137,21 +141,13 @@ static int validate_jobs(const lsb_job *jobs, int n_jobs, int op_mode) {
     return LSB_OK;
 }
 
-// What a filled job table holds, for the launch.
-struct TableInfo {
-    uint64_t tiles = 0;
-    bool has_extract = false, has_embed = false, has_raw = false;
-    int cls = 0;            // kernel class (see lsb_batch_device.hpp)
-    size_t used_bytes = 0;  // header + (n_jobs + 1) records
-};
-
-// Fill a job table (header, records, sentinel) at `host` for validated
-// jobs: per-job status for work the host can already refuse, tile counts
-// and their exclusive prefix, the kernel class.  The header's tile counter
-// is zero, so uploading the table resets it.
+// Fill a job table (records, first tile ids, map) at `host` for validated
+// jobs: per-job status for work the host can already refuse, tile counts and
+// their exclusive prefix, the kernel class.
 static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_t tv, uint8_t *host) {
-    PlanHeader *h = (PlanHeader *)host;
-    DevJob *d = (DevJob *)(host + sizeof(PlanHeader));
+    const TableLayout lay = table_layout((uint64_t)n_jobs);
+    DevJob *d = (DevJob *)host;
+    uint64_t *first = (uint64_t *)(host + lay.first_off);
     TableInfo t;
     uint64_t tiles = 0;
     for (int i = 0; i < n_jobs; ++i) {
@@ -168,7 +164,7 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
         D.len = D.raw ? 0 : J.len;  // what the kernel reports in len_dev
         D.k = J.k;
         D.op = op;
-        D.tile_begin = tiles;
+        first[i] = tiles;
         D.status = LSB_OK;
         uint64_t vectors = ceil_div(J.n, 16);
         if (D.raw) {
@@ -210,15 +206,18 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
         // stego write), so it covers twice the vectors to carry the same
         // traffic per job lookup
         const uint64_t jtv = op == LSB_OP_EMBED ? (uint64_t)tv : 2 * (uint64_t)tv;
-        tiles += ceil_div(vectors, jtv);
+        const uint64_t jt = ceil_div(vectors, jtv);
+        t.has_empty |= jt == 0;
+        tiles += jt;
     }
-    DevJob &S = d[n_jobs];  // sentinel
-    memset(&S, 0, sizeof S);
-    S.tile_begin = tiles;
-    memset(h, 0, sizeof *h);
-    h->n_jobs = (uint64_t)n_jobs;
-    h->total_tiles = tiles;
-    h->tile_vectors = (uint64_t)tv;
+    for (int i = 0; i < kFirstPad; ++i) first[n_jobs + i] = ~0ull;
+    while ((tiles >> t.map_shift) >= lay.map_max) ++t.map_shift;
+    uint32_t *map = (uint32_t *)(host + lay.map_off);
+    const uint64_t entries = tiles ? ((tiles - 1) >> t.map_shift) + 1 : 0;
+    for (uint64_t i = 0, j = 0; i < entries; ++i) {
+        while (first[j + 1] <= (i << t.map_shift)) ++j;  // ends at the ~0 behind the last job
+        map[i] = (uint32_t)j;
+    }
     t.tiles = tiles;
     if (n_jobs > 0) {
         bool same = true;
@@ -226,17 +225,42 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
         for (int i = 1; i < n_jobs && same; ++i) same = d[i].op == d[0].op && d[i].k == d[0].k;
         for (int i = 1; i < n_jobs && same_op; ++i) same_op = d[i].op == d[0].op;
         if (same) t.cls = 1 + 8 * d[0].op + (d[0].k - 1);
-        else if (same_op && d[0].op == LSB_OP_EXTRACT) t.cls = kClsExtractAnyK;
+        else if (same_op) t.cls = d[0].op == LSB_OP_EXTRACT ? kClsExtractAnyK : kClsEmbedAnyK;
     }
-    t.used_bytes = sizeof(PlanHeader) + sizeof(DevJob) * ((size_t)n_jobs + 1);
+    t.used_bytes = lay.map_off + 4 * entries;
     return t;
 }
 
-// Grid of the persistent kernel: capped at blocks_per_cu blocks per CU,
-// never more blocks than tiles.
+// One block per tile, capped at blocks_per_cu blocks per CU (0: no cap) and at
+// the 2^32 - 1 threads of a launch.
 static unsigned main_grid_for(const lsb_launch_cfg &cfg, uint64_t total_tiles) {
-    const uint64_t cap_blocks = (uint64_t)(cfg.blocks_per_cu > 0 ? cfg.blocks_per_cu : 8) * (uint64_t)device_cus();
-    return (unsigned)(total_tiles < cap_blocks ? (total_tiles ? total_tiles : 1) : cap_blocks);
+    uint64_t cap = 0xFFFFFFFFull / (uint64_t)cfg.block;
+    if (cfg.blocks_per_cu > 0) cap = std::min(cap, (uint64_t)cfg.blocks_per_cu * (uint64_t)device_cus());
+    return (unsigned)std::min(cap, std::max<uint64_t>(total_tiles, 1));
+}
+
+// Launch the kernel of a filled, uploaded table.
+static hipError_t launch_batch(const lsb_launch_cfg &cfg, const TableInfo &t, int n_jobs, int64_t tv,
+                               const uint8_t *table, const uint8_t *cover_arena, uint8_t *stego_arena,
+                               uint8_t *msg_arena, uint32_t *len_dev, int32_t *status_dev, hipStream_t st) {
+    const TableLayout lay = table_layout((uint64_t)n_jobs);
+    BatchArgs a{};
+    a.jobs = (const DevJob *)table;
+    a.first = (const uint64_t *)(table + lay.first_off);
+    a.map = (const uint32_t *)(table + lay.map_off);
+    a.map_shift = t.map_shift;
+    a.n_jobs = (uint64_t)n_jobs;
+    a.total_tiles = t.tiles;
+    a.tile_vectors = (uint64_t)tv;
+    a.cover_arena = cover_arena;
+    a.stego_arena = stego_arena;
+    a.msg_arena = msg_arena;
+    a.len_dev = len_dev;
+    a.status_dev = status_dev;
+    a.empty_jobs = t.has_empty;
+    void *argv[] = {&a};
+    return hipLaunchKernel((const void *)batch_fn(cfg.unroll, cfg.nontemporal, t.cls, t.has_raw),
+                           dim3(main_grid_for(cfg, t.tiles)), dim3(cfg.block), argv, 0, st);
 }
 
 static int64_t batch_tile_vectors() {
@@ -250,7 +274,7 @@ int lsb_plan_create(lsb_plan **out, const lsb_job *jobs, int n_jobs, int op) {
     clear_error();
     if (!out) return fail(LSB_E_ARG, "lsb_plan_create: null plan pointer");
     *out = nullptr;
-    if (n_jobs < 1 || n_jobs > (1 << 24)) return fail(LSB_E_ARG, "lsb_plan_create: n_jobs=%d", n_jobs);
+    if (n_jobs < 1 || n_jobs > kMaxJobs) return fail(LSB_E_ARG, "lsb_plan_create: n_jobs=%d", n_jobs);
     if (op != LSB_OP_EMBED && op != LSB_OP_EXTRACT && op != LSB_OP_MIXED)
         return fail(LSB_E_ARG, "lsb_plan_create: op=%d", op);
     lsb_plan *p = new (std::nothrow) lsb_plan();
@@ -259,7 +283,7 @@ int lsb_plan_create(lsb_plan **out, const lsb_job *jobs, int n_jobs, int op) {
     if (e != hipSuccess) return delete p, hip_fail(e, "hipGetDevice");
     p->max_jobs = n_jobs;
     p->op_mode = op;
-    p->table_bytes = sizeof(PlanHeader) + sizeof(DevJob) * ((size_t)n_jobs + 1);
+    p->table_bytes = (size_t)table_layout((uint64_t)n_jobs).bytes;
     e = hipHostMalloc((void **)&p->host, p->table_bytes, hipHostMallocDefault);
     if (e != hipSuccess) return delete p, fail(LSB_E_NOMEM, "lsb_plan_create: hipHostMalloc failed");
     e = hipMalloc((void **)&p->dev, p->table_bytes);
@@ -268,7 +292,6 @@ int lsb_plan_create(lsb_plan **out, const lsb_job *jobs, int n_jobs, int op) {
     e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming);
     if (e != hipSuccess) return (void)hipFree(p->dev), (void)hipHostFree(p->host), delete p, hip_fail(e, "hipEventCreate");
     memset(p->host, 0, p->table_bytes);
-    p->used_bytes = sizeof(PlanHeader) + sizeof(DevJob);
     if (jobs) {
         const int rc = lsb_plan_update(p, jobs, n_jobs);
         if (rc != LSB_OK) {
@@ -295,20 +318,14 @@ int lsb_plan_update(lsb_plan *p, const lsb_job *jobs, int n_jobs) {
         hipError_t e = hipEventSynchronize(p->done);
         if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize(plan)");
     }
-    const TableInfo t = fill_table(jobs, n_jobs, p->op_mode, tv, p->host);
+    p->info = fill_table(jobs, n_jobs, p->op_mode, tv, p->host);
     p->n_jobs = n_jobs;
-    p->total_tiles = t.tiles;
-    p->has_extract = t.has_extract;
-    p->has_embed = t.has_embed;
-    p->has_raw = t.has_raw;
-    p->cls = t.cls;
     p->tile_vectors = tv;
-    p->used_bytes = t.used_bytes;
     p->table_dirty = true;
     return LSB_OK;
 }
 
-int64_t lsb_plan_tiles(const lsb_plan *p) { return p ? (int64_t)p->total_tiles : fail(LSB_E_ARG, "null plan"); }
+int64_t lsb_plan_tiles(const lsb_plan *p) { return p ? (int64_t)p->info.tiles : fail(LSB_E_ARG, "null plan"); }
 
 int lsb_job_extents(const lsb_job *jobs, int n_jobs, int op, uint64_t *extents) {
     clear_error();
@@ -356,9 +373,9 @@ int lsb_plan_run(lsb_plan *p, const uint8_t *cover_arena, uint8_t *stego_arena, 
     if (!p) return fail(LSB_E_ARG, "lsb_plan_run: null plan");
     if (p->n_jobs == 0) return LSB_OK;
     if (!status_dev) return fail(LSB_E_ARG, "lsb_plan_run: null status_dev");
-    if (p->has_extract && !len_dev) return fail(LSB_E_ARG, "lsb_plan_run: extract jobs need len_dev");
+    if (p->info.has_extract && !len_dev) return fail(LSB_E_ARG, "lsb_plan_run: extract jobs need len_dev");
     if (!stego_arena || !msg_arena) return fail(LSB_E_ARG, "lsb_plan_run: null arena");
-    if (p->has_embed && !cover_arena) return fail(LSB_E_ARG, "lsb_plan_run: embed jobs need a cover arena");
+    if (p->info.has_embed && !cover_arena) return fail(LSB_E_ARG, "lsb_plan_run: embed jobs need a cover arena");
     if (((uintptr_t)cover_arena | (uintptr_t)stego_arena | (uintptr_t)msg_arena) & 255)
         return fail(LSB_E_ARG, "lsb_plan_run: arena base pointers must be 256-byte aligned");
     int dev = -1;
@@ -366,7 +383,7 @@ int lsb_plan_run(lsb_plan *p, const uint8_t *cover_arena, uint8_t *stego_arena, 
     if (de != hipSuccess) return hip_fail(de, "hipGetDevice");
     if (dev != p->device) return fail(LSB_E_ARG, "lsb_plan_run: plan belongs to device %d, current is %d", p->device, dev);
     int64_t tv;
-    const lsb_launch_cfg cfg = batch_cfg_for(p->has_embed, p->has_extract, &tv);
+    const lsb_launch_cfg cfg = batch_cfg_for(p->info.has_embed, p->info.has_extract, &tv);
     if (tv != p->tile_vectors) return fail(LSB_E_ARG, "lsb_plan_run: tile size changed since lsb_plan_update");
     hipStream_t st = (hipStream_t)stream;
     // A captured run would replay its upload and kernel outside the plan's
@@ -379,30 +396,24 @@ int lsb_plan_run(lsb_plan *p, const uint8_t *cover_arena, uint8_t *stego_arena, 
     if (capture != hipStreamCaptureStatusNone)
         return fail(LSB_E_ARG, "lsb_plan_run: the stream is capturing a graph (a captured run would replay outside "
                                "the plan's tracking of its table and runs)");
-    const BatchFn fn = batch_fn(cfg.unroll, cfg.nontemporal, p->cls, p->has_raw);
-    const PlanHeader *hdr = (const PlanHeader *)p->dev;
-    const DevJob *jobs = (const DevJob *)(p->dev + sizeof(PlanHeader));
     hipError_t e;
     if (p->ran && st != p->last_stream) {
-        // every run shares the device job table and its tile counters: a run
-        // on another stream starts only after the previous run has finished
+        // every run shares the device job table: a run on another stream starts only after the previous run has finished
         e = hipStreamWaitEvent(st, p->done, 0);
         if (e != hipSuccess) return hip_fail(e, "hipStreamWaitEvent(plan)");
     }
-    // upload the job table only when it changed since the last upload (the
-    // kernel's last block resets the tile counters either way)
+    // upload the job table only when it changed since the last upload
     const bool upload = p->table_dirty;
     if (upload) {
-        e = hipMemcpyAsync(p->dev, p->host, p->used_bytes, hipMemcpyHostToDevice, st);
+        e = hipMemcpyAsync(p->dev, p->host, p->info.used_bytes, hipMemcpyHostToDevice, st);
         if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(job table)");
     }
-    void *argv[] = {&hdr, &jobs, &cover_arena, &stego_arena, &msg_arena, &len_dev, &status_dev};
-    e = hipLaunchKernel((const void *)fn, dim3(main_grid_for(cfg, p->total_tiles)), dim3(cfg.block), argv, 0, st);
+    e = launch_batch(cfg, p->info, p->n_jobs, tv, p->dev, cover_arena, stego_arena, msg_arena, len_dev, status_dev, st);
     if (e != hipSuccess) {
         // an enqueued upload still reads the pinned mirror: let it finish
         // before a later update may refill the mirror
         if (upload) (void)hipStreamSynchronize(st);
-        return hip_fail(e, "persistent kernel launch");
+        return hip_fail(e, "batched kernel launch");
     }
     e = hipEventRecord(p->done, st);
     if (e != hipSuccess) {
@@ -421,7 +432,7 @@ int lsb_embed_batch(lsb_plan *p, const uint8_t *cover_arena, uint8_t *stego_aren
                     int32_t *status_dev, void *stream) {
     clear_error();
     if (!p) return fail(LSB_E_ARG, "lsb_embed_batch: null plan");
-    if (p->has_extract) return fail(LSB_E_ARG, "lsb_embed_batch: the plan holds extract jobs");
+    if (p->info.has_extract) return fail(LSB_E_ARG, "lsb_embed_batch: the plan holds extract jobs");
     if (p->n_jobs && !cover_arena) return fail(LSB_E_ARG, "lsb_embed_batch: null cover arena");
     // embed jobs only read the message arena
     return lsb_plan_run(p, cover_arena, stego_arena, const_cast<uint8_t *>(msg_arena), nullptr, status_dev, stream);
@@ -431,7 +442,7 @@ int lsb_extract_batch(lsb_plan *p, const uint8_t *stego_arena, uint8_t *msg_aren
                       int32_t *status_dev, void *stream) {
     clear_error();
     if (!p) return fail(LSB_E_ARG, "lsb_extract_batch: null plan");
-    if (p->has_embed) return fail(LSB_E_ARG, "lsb_extract_batch: the plan holds embed jobs");
+    if (p->info.has_embed) return fail(LSB_E_ARG, "lsb_extract_batch: the plan holds embed jobs");
     if (p->n_jobs && !len_dev) return fail(LSB_E_ARG, "lsb_extract_batch: null len_dev");
     // extract jobs only read the stego arena
     return lsb_plan_run(p, nullptr, const_cast<uint8_t *>(stego_arena), msg_arena, len_dev, status_dev, stream);
@@ -490,12 +501,8 @@ int lsb_batch_run_static(const lsb_job *jobs, int n_jobs, int op, const uint8_t 
     if (t.has_embed && !cover_arena) return fail(LSB_E_ARG, "lsb_batch_run_static: embed jobs need a cover arena");
     e = hipMemcpyAsync(table, g_static_host, t.used_bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(static job table)");
-    const PlanHeader *hdr = (const PlanHeader *)table;
-    const DevJob *dj = (const DevJob *)(table + sizeof(PlanHeader));
-    const BatchFn fn = batch_fn(cfg.unroll, cfg.nontemporal, t.cls, t.has_raw);
-    void *main_args[] = {&hdr, &dj, &cover_arena, &stego_arena, &msg_arena, &len_dev, &status_dev};
-    e = hipLaunchKernel((const void *)fn, dim3(main_grid_for(cfg, t.tiles)), dim3(cfg.block), main_args, 0, st);
-    if (e != hipSuccess) return hip_fail(e, "persistent kernel launch");
+    e = launch_batch(cfg, t, n_jobs, tv, table, cover_arena, stego_arena, msg_arena, len_dev, status_dev, st);
+    if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
     return LSB_OK;
 }
 
@@ -507,7 +514,6 @@ int lsb_batch_tune_get(lsb_launch_cfg *cfg, int64_t *tile_vectors) {
 }
 
 static bool batch_cfg_valid(const lsb_launch_cfg *cfg) {
-    // one wave of every block hands out tiles, the others stream them
     return cfg && cfg_valid(*cfg) && cfg->block >= 128;
 }
 

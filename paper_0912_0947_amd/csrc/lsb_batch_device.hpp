@@ -1,5 +1,5 @@
 // lsb_batch_device.hpp -- device side of the batched embed/extract: the job
-// table records and the persistent kernel, shared by the translation unit of
+// table and the batched kernel, shared by the translation unit of
 // header-only plans and the one of plans with raw-slice jobs.
 #pragma once
 
@@ -11,30 +11,11 @@
 
 namespace lsb {
 
-// The tile counter has a 128-byte cache line of its own: sharing a line with
-// the job records that every block reads made each atomic contend with those
-// reads (a one-job batch ran at 40 % of a many-job batch).  Both counters
-// are zero in an uploaded table, and the last block of each run sets them
-// back to zero, so a run whose table is already on the device starts from
-// zero without an upload.
-struct PlanHeader {
-    uint64_t n_jobs;
-    uint64_t total_tiles;
-    uint64_t tile_vectors;
-    uint64_t pad0[13];
-    uint64_t next_tile;    // tile counter of the persistent kernel
-    uint64_t blocks_done;  // blocks whose producer has taken its last tile id this run
-    uint64_t pad1[14];
-};
-static_assert(sizeof(PlanHeader) == 256 && offsetof(PlanHeader, next_tile) == 128 &&
-                  offsetof(PlanHeader, blocks_done) == 136,
-              "counters on their own line, job records 256-byte aligned");
-
 struct DevJob {
     uint64_t cover_off, stego_off, msg_off, n;
-    uint64_t cap_bits;    // header extract: msg_cap; raw: end bit (embed: stream_bits, extract: e)
-    uint64_t tile_begin;  // tiles of jobs before this one; entry n_jobs = total
-    uint64_t t0;          // raw: logical field index of buffer byte 0; header jobs: 0
+    uint64_t cap_bits;  // header extract: msg_cap; raw: end bit (embed: stream_bits, extract: e)
+    uint64_t t0;        // raw: logical field index of buffer byte 0; header jobs: 0
+    uint64_t pad;
     uint32_t len;
     uint8_t k, op;
     int8_t status;  // host-validated status; header extract: decoded on device
@@ -42,6 +23,43 @@ struct DevJob {
 };
 static_assert(sizeof(DevJob) == 64, "DevJob is one 64-byte record");
 static_assert(sizeof(lsb_job) == 64 && offsetof(lsb_job, len) == 56, "lsb_job layout of the C ABI");
+
+// The job table: the records, every job's first tile id (then kFirstPad
+// entries of ~0), and a map from tile ids to jobs: entry i names the job that
+// holds tile i << map_shift, with the smallest shift whose map fits 4 entries
+// per job plus 4096.  A map of shift 0 names a tile's job outright; a larger
+// one (big covers) leaves the jobs that begin inside the entry's tiles.
+constexpr int kMaxJobs = 1 << 24;
+constexpr int kFirstPad = 8;
+
+struct TableLayout {
+    uint64_t first_off, map_off;  // byte offsets behind the records
+    uint64_t map_max;             // entries
+    uint64_t bytes;               // with a full map
+};
+
+__host__ __device__ constexpr TableLayout table_layout(uint64_t n_jobs) {
+    TableLayout t{};
+    t.first_off = sizeof(DevJob) * n_jobs;
+    t.map_off = t.first_off + 8 * (n_jobs + kFirstPad);
+    t.map_max = 4 * n_jobs + 4096;
+    t.bytes = t.map_off + 4 * t.map_max;
+    return t;
+}
+
+// Everything a run needs, by value.
+struct BatchArgs {
+    const DevJob *jobs;
+    const uint64_t *first;
+    const uint32_t *map;
+    uint64_t n_jobs, total_tiles, tile_vectors;
+    const uint8_t *cover_arena;
+    uint8_t *stego_arena, *msg_arena;
+    uint32_t *len_dev;
+    int32_t *status_dev;
+    int32_t map_shift;
+    int32_t empty_jobs;  // some job has no tile
+};
 
 // One tile of a job: ranges with k known at compile time, then the walk
 // over the tile's vectors.
@@ -64,22 +82,19 @@ __device__ __forceinline__ void extract_tile(const Span &s, uint64_t v_begin, ui
 }
 
 // Job classes of a plan.  CLS = 1 + 8*op + (k - 1): every job has that
-// (op, k), and only its walker is compiled in.  CLS = 17: every job is an
-// extract, k dispatched by a switch over the eight extract walkers (61 VGPRs
-// at two vectors per lane, so two 1024-thread blocks fit a CU; the same for
-// the embed walkers needs more than the sixteen-way switch and spills).
-// CLS = 0: (op, k) read from each job, a switch over all sixteen.
+// (op, k), and only its walker is compiled in.  CLS = 17 / 18: every job is
+// an extract / an embed, k dispatched by a switch over the eight walkers of
+// that kind.  CLS = 0: (op, k) read from each job, a switch over all sixteen.
 // Header and raw-slice jobs share the walkers: only the span's stream fields
 // differ.  RAW = false compiles the raw-slice case out (the plan has none):
-// the header span's constant t0, header length and dword stream side then
-// fold into the walk.
-constexpr int kClsExtractAnyK = 17, kClasses = 18;
+// the header span's constant t0 and header length then fold into the walk.
+constexpr int kClsExtractAnyK = 17, kClsEmbedAnyK = 18, kClasses = 19;
 
 template <int UNR, bool NT, int CLS, bool RAW>
 __device__ __forceinline__ void run_tile(const DevJob &J, uint64_t v_begin, uint64_t tile_vectors,
                                          const uint8_t *cover_arena, uint8_t *stego_arena, uint8_t *msg_arena,
                                          uint32_t len, uint32_t wave, uint32_t n_waves, uint32_t lane) {
-    constexpr bool EMB = CLS == 0 || (CLS >= 1 && CLS <= 8);
+    constexpr bool EMB = CLS == 0 || CLS == kClsEmbedAnyK || (CLS >= 1 && CLS <= 8);
     constexpr bool EXT = CLS == 0 || CLS == kClsExtractAnyK || (CLS >= 9 && CLS <= 16);
     constexpr int KC = CLS >= 1 && CLS <= 16 ? (CLS - 1) % 8 + 1 : 0;  // fixed k, 0: any
     Span s{};
@@ -137,76 +152,13 @@ __device__ __forceinline__ void run_tile(const DevJob &J, uint64_t v_begin, uint
     }
 }
 
-// Waves per SIMD the launch bound asks for.  A 1024-thread block puts 4
-// waves on each SIMD (so at most 128 VGPRs), and anything from 4 to 7 keeps
-// one block per CU; only 8 (64 VGPRs) fits two.  8 at one vector per lane
-// (about 30-40 VGPRs) and for the extract-any-k class at two (47 VGPRs; with
-// raw slices it would spill under 64 and takes 6); 6 for the others at two,
-// 5 for the raw-capable kernels with the widest walkers (all sixteen behind
-// the switch: 85 VGPRs; k = 1 embed), where 6 would spill; 4 at four (the
-// extract-any-k class then uses 88 VGPRs, 97 with raw slices: one block per
-// CU).
+// Waves per SIMD the launch bound asks for: as many as each kernel's walkers
+// fit without spilling (the sixteen-way switch holds every walker at once).
 template <int UNR, int CLS, bool RAW>
 constexpr int batch_min_waves() {
     if constexpr (UNR == 1) return 8;
     else if constexpr (UNR == 2) return CLS == kClsExtractAnyK && !RAW ? 8 : (RAW && CLS <= 1 ? 5 : 6);
     else return 4;
-}
-
-// Tile hand-off inside a block.  Wave 0 is the block's producer and does no
-// streaming itself: it takes the next tile id from the plan's counter,
-// resolves the tile's job (forward search over the tile prefix, 64 jobs per
-// ballot; jobs only move forward as the tile id grows), reads the job record
-// (and, for a header extract job, decodes the job's length header), and
-// publishes all of it in a slot of a two-slot LDS ring.  The producer that
-// takes a job's first tile also reports the job's length and status; jobs
-// without tiles are reported by a sweep over the job table that every
-// producer runs once.  The other waves (the workers) read their next tile
-// from the ring when they finish the current one, so they never wait for
-// each other at a tile boundary, and the latency of the counter, the search
-// and the record reads is spent by the producer while the workers stream.
-// The producer publishes tile m + 1 once every worker has taken tile m (the
-// slot it overwrites was read before that), so a block holds at most one
-// tile beyond the one its slowest worker is on.  Every wait is
-// bounded (kSpinLimit polls): a wave whose partner never answers gives up
-// instead of hanging the device (its tiles are then left undone).
-constexpr int kRing = 2;
-constexpr uint32_t kSpinLimit = 1u << 26;
-
-struct TileSlot {
-    DevJob job;       // the tile's job record
-    uint64_t tile;    // global tile id; >= total ends the block
-    uint32_t len;     // header extract: decoded message length
-    uint32_t run;     // 1: the job has work (status OK)
-};
-
-// Ordering of the hand-off.  The LDS instructions of one wave execute in
-// the order they are issued, and a wave observes another wave's LDS write
-// once it has executed.  So the ring needs only relaxed LDS accesses kept in
-// program order by compiler barriers: the producer writes a slot, then its
-// sequence number; a worker reads the sequence number, then the slot, then
-// counts itself as a reader.  (Release/acquire atomics would also order the
-// waves' global memory traffic: a worker would wait for its previous tile's
-// stores to complete at every tile boundary.)
-__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
-
-__device__ __forceinline__ uint32_t lds_read(const uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ void lds_write(uint32_t *p, uint32_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Wait (wave-uniform) until *p == want; false if the limit ran out.
-__device__ __forceinline__ bool lds_wait_eq(const uint32_t *p, uint32_t want) {
-    for (uint32_t i = 0; i < kSpinLimit; ++i) {
-        const uint32_t v = lds_read(p);
-        lds_order();
-        if (v == want) return true;
-        __builtin_amdgcn_s_sleep(1);
-    }
-    return false;
 }
 
 __device__ __forceinline__ uint32_t uniform32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -240,150 +192,113 @@ __device__ __forceinline__ JobReport job_report(const DevJob &J, const uint8_t *
 }
 
 // Reports of the jobs without tiles (refused on the host, empty slices, and
-// header extract jobs whose cover holds fewer than 32 bits), lane-parallel
-// over the table: block b's producer takes jobs 64b + lane, then every
-// 64 G-th.  No tile is ever handed out for these jobs, so nothing else
-// writes their entries.  A header extract job the host let through has a
-// tile whenever k n >= 32, so one without tiles is refused here.
-__device__ __forceinline__ void report_empty_jobs(const DevJob *jobs, uint64_t n_jobs, uint32_t *len_dev,
-                                                  int32_t *status_dev, uint32_t lane) {
-    for (uint64_t j = (uint64_t)blockIdx.x * 64 + lane; j < n_jobs; j += (uint64_t)gridDim.x * 64) {
-        const DevJob &J = jobs[j];
-        if (J.tile_begin != jobs[j + 1].tile_begin) continue;  // the producer of its first tile reports it
+// header extract jobs whose cover holds fewer than 32 bits), one thread per
+// job over the grid.  No tile is ever handed out for these jobs, so nothing
+// else writes their entries.  A header extract job the host let through has
+// a tile whenever k n >= 32, so one without tiles is refused here.
+__device__ __forceinline__ void report_empty_jobs(const BatchArgs &a) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < a.n_jobs; j += stride) {
+        const uint64_t end = j + 1 < a.n_jobs ? a.first[j + 1] : a.total_tiles;
+        if (a.first[j] != end) continue;  // the block of its first tile reports it
+        const DevJob &J = a.jobs[j];
         uint32_t len = J.len;
         int32_t status = J.status;
         if (J.op == LSB_OP_EXTRACT && !J.raw && status == LSB_OK) {
             len = 0;
             status = LSB_E_HEADER;
         }
-        if (len_dev) len_dev[j] = len;
-        status_dev[j] = status;
+        if (a.len_dev) a.len_dev[j] = len;
+        a.status_dev[j] = status;
     }
 }
 
-// A producer is done with the counter (lane 0): the last one of the grid
-// sets both counters back to zero for the plan's next run.  Every producer
-// has taken its last tile id before it counts itself (its atomics return
-// values that it has used), so after the last count nothing else touches
-// the counters in this run.
-__device__ __forceinline__ void producer_done(const PlanHeader *hdr) {
-    PlanHeader *h = const_cast<PlanHeader *>(hdr);
-    const unsigned long long before = atomicAdd((unsigned long long *)&h->blocks_done, 1ull);
-    if (before == (unsigned long long)gridDim.x - 1) {
-        __hip_atomic_store(&h->next_tile, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&h->blocks_done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+// Read-only table entries at wave-uniform places, through the scalar cache:
+// the table does not change while a kernel runs, and scalar loads have a
+// counter of their own, so a lookup never waits for the wave's stores.
+template <typename T>
+using Uniform = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ Uniform<T> uniform_ptr(const T *p) {
+    return (Uniform<T>)(uintptr_t)p;
 }
 
-// Persistent kernel: tiles come from one counter in arrival order, so the
-// tiles in flight at any moment are neighbours in the arenas (a static b,
-// b + G, ... order lets blocks drift apart over the run).  Blocks have at
-// least two waves (one producer, at least one worker).
-template <int UNR, bool NT, int CLS, bool RAW>
-__global__ void __launch_bounds__(1024, (batch_min_waves<UNR, CLS, RAW>()))
-    lsb_batch_kernel(const PlanHeader *hdr, const DevJob *jobs, const uint8_t *cover_arena, uint8_t *stego_arena,
-                     uint8_t *msg_arena, uint32_t *len_dev, int32_t *status_dev) {
-    __shared__ TileSlot ring[kRing];
-    __shared__ uint32_t seq[kRing];      // iteration whose tile the slot holds
-    __shared__ uint32_t readers[kRing];  // workers that have read the slot's current content
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = threadIdx.x >> 6;
-    const uint32_t workers = (blockDim.x >> 6) - 1;
-    const uint64_t total = hdr->total_tiles;
-    if (threadIdx.x < kRing) {
-        seq[threadIdx.x] = ~0u;
-        readers[threadIdx.x] = workers;  // free
-    }
-    __syncthreads();
-
-    if (wave == 0) {
-        // ---- producer
-        unsigned long long *counter = (unsigned long long *)&const_cast<PlanHeader *>(hdr)->next_tile;
-        const uint64_t n_jobs = hdr->n_jobs;
-        uint64_t j = 0;  // job search cursor
-        uint64_t t = 0;
-        if (lane == 0) t = atomicAdd(counter, 1ull);
-        for (uint32_t m = 0;; ++m) {
-            t = uniform64(t);
-            const uint32_t sl = m % kRing;
-            uint32_t run = 0, len = 0;
-            DevJob J{};
-            if (t < total) {
-                // largest j with jobs[j].tile_begin <= t (entry n_jobs holds total > t)
-                for (;;) {
-                    const uint64_t idx = j + 1 + lane;
-                    const uint64_t tb = idx <= n_jobs ? jobs[idx].tile_begin : ~0ull;
-                    const uint64_t below = __ballot(tb <= t);
-                    const uint32_t cnt = (uint32_t)__popcll(below);
-                    j += cnt;
-                    if (cnt < 64) break;
-                }
-                j = uniform64(j);
-                J = jobs[j];
-                const JobReport r = job_report(J, stego_arena, lane);
-                run = r.status == LSB_OK;
-                len = r.len;
-                if (t == J.tile_begin && lane == 0) {  // the job's first tile: report the job
-                    if (len_dev) len_dev[j] = r.len;
-                    status_dev[j] = r.status;
-                }
-            }
-            // every worker must have taken tile m - 1 (and so every earlier one)
-            if (m && !lds_wait_eq(&readers[(m - 1) % kRing], workers)) {
-                if (lane == 0) producer_done(hdr);
-                return;
-            }
-            if (lane == 0) {
-                if (t < total) ring[sl].job = J;
-                ring[sl].tile = t;
-                ring[sl].len = len;
-                ring[sl].run = run;
-                lds_write(&readers[sl], 0);
-                lds_order();
-                lds_write(&seq[sl], m);
-            }
-            // after the first hand-off, so that the workers start at once
-            if (m == 0) report_empty_jobs(jobs, n_jobs, len_dev, status_dev, lane);
-            if (t >= total) {  // the end mark is out
-                if (lane == 0) producer_done(hdr);
-                return;
-            }
-            if (lane == 0) t = atomicAdd(counter, 1ull);
+// The job of tile t, and its first tile id: the largest j with first[j] <= t.
+// One map entry, then the first tile ids from there on: usually the entry's
+// own job or one of the next few; where a group of tiles holds many small
+// jobs, 64 per step and ballot.
+__device__ __forceinline__ uint64_t find_job(const BatchArgs &a, uint64_t t, uint32_t lane, uint64_t *first_tile) {
+    uint64_t j = uniform_ptr(a.map)[t >> a.map_shift];
+    const Uniform<uint64_t> f = uniform_ptr(a.first) + j;
+    uint64_t ft = f[0];
+    uint32_t step = 0;
+#pragma unroll
+    for (int i = 1; i < kFirstPad; ++i) {
+        const uint64_t x = f[i];
+        if (x <= t) {
+            step = i;
+            ft = x;
         }
     }
+    j += step;
+    if (step == kFirstPad - 1) {
+        for (;;) {
+            const uint64_t idx = j + 1 + lane;
+            const uint64_t tb = idx < a.n_jobs ? a.first[idx] : ~0ull;
+            const uint32_t cnt = (uint32_t)__popcll(__ballot(tb <= t));
+            j += cnt;
+            if (cnt < 64) break;
+        }
+        j = uniform64(j);
+        ft = uniform64(a.first[j]);
+    }
+    *first_tile = ft;
+    return j;
+}
 
-    // ---- workers
-    const uint64_t tv_embed = hdr->tile_vectors;
-    for (uint32_t m = 0;; ++m) {
-        const uint32_t sl = m % kRing;
-        if (!lds_wait_eq(&seq[sl], m)) return;
-        // the slot, read into wave-uniform registers
-        const uint64_t tile = uniform64(ring[sl].tile);
+// One block per tile: each wave finds the tile's job through the map and
+// streams its share of the tile.  HBM bounds it, as the plain kernels: blocks
+// of other tiles stream while one looks its job up, and a wave ends after its
+// last store without waiting for it.  Tiles go to the XCDs in runs of 16
+// (xcd_run_block): neighbours share lines at their ends, the table entries and
+// an L2 (extract of one 1.6 GB job at k = 1: 353 us in launch order, 309-314
+// us in runs).  A grid capped below the tile count walks the tiles with a
+// stride.  Embed + extract, against persistent blocks whose producer wave took
+// tiles from one counter and handed them to 15 workers: 4096 covers of
+// 64..256 px 216 -> 140 us, 256 covers of 64..4096 px 940 -> 886 us (6.2
+// TB/s), 120 frames of 1080p 340 -> 317 us.  The tile is one step of the
+// block: with two steps the second waits for the first one's stores (256
+// covers' embed 646 us at 512 vectors a tile, 678 us at 1024).
+template <int UNR, bool NT, int CLS, bool RAW>
+__global__ void __launch_bounds__(1024, (batch_min_waves<UNR, CLS, RAW>())) lsb_batch_kernel(BatchArgs a) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = uniform32(threadIdx.x >> 6);
+    const uint32_t waves = blockDim.x >> 6;
+    if (a.empty_jobs) report_empty_jobs(a);
+    for (uint64_t t = xcd_run_block(blockIdx.x, gridDim.x); t < a.total_tiles; t += gridDim.x) {
+        uint64_t first_tile;
+        const uint64_t j = find_job(a, t, lane, &first_tile);
         DevJob J;
         {
-            const uint32_t *src = reinterpret_cast<const uint32_t *>(&ring[sl].job);
+            const Uniform<uint32_t> src = uniform_ptr(reinterpret_cast<const uint32_t *>(a.jobs + j));
             uint32_t *dst = reinterpret_cast<uint32_t *>(&J);
 #pragma unroll
-            for (int i = 0; i < (int)(sizeof(DevJob) / 4); ++i) dst[i] = uniform32(src[i]);
+            for (int i = 0; i < (int)(sizeof(DevJob) / 4); ++i) dst[i] = src[i];
         }
-        const uint32_t len = uniform32(ring[sl].len);
-        const uint32_t run = uniform32(ring[sl].run);
-        lds_order();
-        if (lane == 0) __hip_atomic_fetch_add(&readers[sl], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (tile >= total) return;
-        if (run) {
-            // an extract tile covers twice the vectors of an embed tile; the
-            // workers' shares of a tile rotate from tile to tile
-            const uint64_t tv = J.op == LSB_OP_EXTRACT ? 2 * tv_embed : tv_embed;
-            const uint32_t w = (wave - 1 + m) % workers;
-            run_tile<UNR, NT, CLS, RAW>(J, (tile - J.tile_begin) * tv, tv, cover_arena, stego_arena, msg_arena, len,
-                                        w, workers, lane);
+        const JobReport r = job_report(J, a.stego_arena, lane);
+        if (t == first_tile && threadIdx.x == 0) {  // the job's first tile: report the job
+            if (a.len_dev) a.len_dev[j] = r.len;
+            a.status_dev[j] = r.status;
         }
+        if (r.status != LSB_OK) continue;
+        // an extract tile covers twice the vectors of an embed tile
+        const uint64_t tv = J.op == LSB_OP_EXTRACT ? 2 * a.tile_vectors : a.tile_vectors;
+        run_tile<UNR, NT, CLS, RAW>(J, (t - first_tile) * tv, tv, a.cover_arena, a.stego_arena, a.msg_arena, r.len,
+                                    wave, waves, lane);
     }
 }
 
-typedef void (*BatchFn)(const PlanHeader *, const DevJob *, const uint8_t *, uint8_t *, uint8_t *, uint32_t *,
-                        int32_t *);
+typedef void (*BatchFn)(BatchArgs);
 
 // Kernel table of one launch shape: entry CLS of the class sequence.
 template <int UNR, bool NT, bool RAW, int... C>

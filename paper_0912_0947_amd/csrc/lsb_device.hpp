@@ -474,6 +474,26 @@ __device__ __forceinline__ uint32_t decode_header(const uint8_t *stego, int k, u
     return __builtin_bitreverse32((uint32_t)m);
 }
 
+// Block order of the embed and extract kernels (launch configuration field
+// `order`; Span.block_order).  Workgroups go to the eight XCDs in turn, so
+// neighbouring blocks sit on different XCDs (each with its own L2), and a
+// line that two neighbours share is moved by both: the embed's
+// stream bytes straddle a line at each end of a block (the 4-byte header sits
+// in front of the message), and an extract block's 2k-byte outputs end
+// inside a line.  Logical blocks are therefore handed out in runs of 16 per
+// XCD (physical block b on XCD b % 8 takes logical block
+// 128 (s / 16) + 16 x + s % 16, s = b / 8): the neighbours inside a run share
+// an L2, and the XCDs still interleave at 16-block granularity (handing each
+// XCD one contiguous eighth removed the shared lines too, but made every
+// XCD stream its own distant region and slowed the grid-stride launches).
+// Blocks past the last whole round of 128 keep their index.
+__device__ __forceinline__ uint32_t xcd_run_block(uint32_t b, uint32_t grid) {
+    constexpr uint32_t kXcds = 8, kRun = 16, kRound = kXcds * kRun;
+    if (b >= grid / kRound * kRound) return b;
+    const uint32_t x = b % kXcds, slot = b / kXcds;
+    return (slot / kRun) * kRound + x * kRun + slot % kRun;
+}
+
 // floor(n*k/8) without overflow.
 __host__ __device__ inline uint64_t room_bytes(uint64_t n, int k) {
     return (n / 8) * (uint64_t)k + ((n % 8) * (uint64_t)k) / 8;

@@ -303,10 +303,10 @@ def tune_batch(log=print, count: int = 4096):
     results = []
     by_tv = {}
     # streaming stores only: the arenas (about 35 GB) are far beyond the cache
-    for tv in (2048, 4096, 8192):
+    for tv in (512, 1024, 2048, 4096):
         for block in (256, 512, 1024):
             for unroll in (1, 2, 4):
-                for bpc in (2, 4, 8):
+                for bpc in (0, 8):
                     batch.tune_set(block, unroll, bpc, 1, tv)
                     pe = batch.Plan(count, api.OP_EMBED, wl.jobs(api.OP_EMBED))
                     px = batch.Plan(count, api.OP_EXTRACT, wl.jobs(api.OP_EXTRACT))

@@ -626,3 +626,43 @@ def test_binding_refuses_buffers_the_jobs_do_not_fit():
     finally:
         pe.close()
         px.close()
+
+
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 127, 4095, 4096, 4097, 8193])
+def test_job_index_levels(count, restore_tiles):
+    """A tile finds its job in an index of 64-entry groups, one level more at
+    65 and at 4097 jobs: tiny covers (with jobs of no tile and jobs of
+    several 64-vector tiles between them) around those counts, each stego
+    against one oracle embed."""
+    batch.tune_set(128, 1, 0, 0, 64)
+    g = inputs.rng(4471, count)
+    n = g.integers(33, 200, size=count)
+    n[g.integers(0, count, size=max(1, count // 50))] = 3000  # three tiles
+    n[-1] = 2100
+    empty = g.random(count) < 0.1
+    empty[-1] = False
+    jobs = batch.make_jobs(count)
+    offs = np.concatenate([[0], np.cumsum([batch.align_up(int(x)) for x in n])])
+    jobs["cover_off"] = jobs["stego_off"] = offs[:-1]
+    jobs["n"], jobs["k"], jobs["op"] = n, 1 + np.arange(count) % 8, OP_EMBED
+    caps = np.array([oracle.capacity(int(a), int(b)) for a, b in zip(n, jobs["k"])])
+    jobs["len"] = np.where(empty, caps + 1, np.maximum(caps - 1, 0))
+    cover = inputs.random_bytes(int(offs[-1]), 4472, count)
+    msg = inputs.random_bytes(4096, 4473, count)  # every job reads the same message bytes
+    cover_d, msg_d = torch.from_numpy(cover).to(DEV), torch.from_numpy(msg).to(DEV)
+    stego_d = torch.full_like(cover_d, 0x5A)
+    status = torch.full((count,), 99, dtype=torch.int32, device=DEV)
+    plan = batch.Plan(count, OP_EMBED, jobs)
+    try:
+        plan.embed_batch(cover_d, stego_d, msg_d, status)
+        got, st = to_host(stego_d), status.cpu().numpy()
+        want = np.full_like(cover, 0x5A)
+        for i in range(count):
+            o, m = int(offs[i]), int(n[i])
+            assert st[i] == (E_CAPACITY if empty[i] else OK), i
+            if not empty[i]:
+                rc, want[o:o + m] = oracle.embed(cover[o:o + m], msg[:int(jobs["len"][i])], int(jobs["k"][i]))
+                assert rc == OK
+        assert_bytes_equal(got, want, "%d jobs" % count)
+    finally:
+        plan.close()
