@@ -7,9 +7,9 @@
 //     reads them (mask the field, shift it down), equal those stream bits, and
 //   - every other bit (above the field; the low bits of a partial last field;
 //     all bits of a byte past the stream) equals the cover's.
-// Both checks go through the extraction side of the method (extract_vec on a
-// whole vector, or the per-byte field read), never through the embedding
-// arithmetic, so an embedding mistake shows up as a mismatch.
+// Both checks go through the extraction side of the method (extract_vec),
+// never through the embedding arithmetic, so an embedding mistake shows up as
+// a mismatch.
 //
 // lsb_verify reads cover, stego and stream once (2n + |S| bytes) and counts
 // wrong stego bytes.  lsb_embed_verify embeds (as lsb_embed) and, in the same
@@ -21,36 +21,6 @@
 #include "lsb_host.hpp"
 
 namespace lsb {
-
-// Stream bits carried by field t: their count nb (0 past the stream) and
-// value v, first bit highest.
-__device__ __forceinline__ uint32_t stream_field(const Span &s, uint64_t t, uint32_t *nb_out) {
-    const uint32_t k = (uint32_t)s.k;
-    const uint64_t first = (uint64_t)k * (s.t0 + t);
-    if (first >= s.bits) {
-        *nb_out = 0;
-        return 0;
-    }
-    const uint64_t left = s.bits - first;
-    const uint32_t nb = left < k ? (uint32_t)left : k;
-    const uint64_t byte = first >> 3;
-    const uint32_t bit = (uint32_t)(first & 7);
-    uint32_t pair = stream_byte(s, byte) << 8;
-    if (bit + nb > 8) pair |= stream_byte(s, byte + 1);
-    *nb_out = nb;
-    return (pair >> (16 - bit - nb)) & ((1u << nb) - 1u);
-}
-
-// 1 if stego byte g at buffer position t is wrong for cover byte c.
-__device__ __forceinline__ uint32_t byte_wrong(const Span &s, uint64_t t, uint32_t c, uint32_t g) {
-    uint32_t nb;
-    const uint32_t v = stream_field(s, t, &nb);
-    if (!nb) return g != c;
-    const uint32_t shift = (uint32_t)s.k - nb;
-    const uint32_t mask = ((1u << nb) - 1u) << shift;
-    const uint32_t read_back = (g & mask) >> shift;  // Section VII step 6 on this byte
-    return (read_back != v) | (((g ^ c) & ~mask & 0xFFu) != 0);
-}
 
 // Wrong bytes of a fast vector (all 16 fields carry K stream bits): extract
 // the stego vector's fields into stream words, compare them with the stream
@@ -101,6 +71,28 @@ __device__ __forceinline__ uint32_t bytes_differ(u32x4 a, u32x4 b) {
     return n;
 }
 
+// Wrong bytes of any vector whose first m bytes are in the buffer and whose
+// fields hold nb stream bits, the chunk w: a field's stream bits are read back
+// through extraction, every other bit of its byte is compared with the cover.
+template <int K>
+__device__ __forceinline__ uint32_t any_wrong(u32x4 c, u32x4 g, uint32_t *w, uint32_t nb, uint32_t m) {
+    uint32_t diff[Chunk<K>::NW];
+    extract_vec<K>(g, diff);
+#pragma unroll
+    for (int i = 0; i < Chunk<K>::NW; ++i) diff[i] ^= w[i];
+    keep_bits<K>(diff, nb);
+    uint32_t bad = 0;
+#pragma unroll
+    for (uint32_t f = 0; f < 16; ++f) {
+        const uint32_t left = nb > K * f ? nb - K * f : 0;
+        const uint32_t vb = left < K ? left : K;  // the field's stream bits, its highest
+        const uint32_t mask = ((1u << vb) - 1u) << (K - vb);
+        const uint32_t kept = ((c[f >> 2] ^ g[f >> 2]) >> (8 * (f & 3))) & 0xFFu & ~mask;
+        bad += f < m && (get_field<K>(diff, (int)f) | kept) != 0;
+    }
+    return bad;
+}
+
 // Sum `bad` over the block (256 threads) and add it to the counter.
 __device__ __forceinline__ void add_block_count(uint32_t bad, unsigned long long *mismatches) {
     for (int off = 32; off > 0; off >>= 1) bad += __shfl_xor(bad, off);
@@ -125,10 +117,10 @@ __device__ __forceinline__ uint32_t verify_one(const Span &s, const Ranges &r, u
     }
     if (u >= r.copy_begin && u < r.copy_end)
         return bytes_differ(load16<true>(s.src + 16 * u), load16<true>(s.dst + 16 * u));
-    uint32_t bad = 0;
-    const uint64_t t_end = 16 * u + 16 < s.n ? 16 * u + 16 : s.n;
-    for (uint64_t t = 16 * u; t < t_end; ++t) bad += byte_wrong(s, t, s.src[t], s.dst[t]);
-    return bad;
+    const uint32_t nb = vector_bits<K>(s, u), m = vector_bytes(s, u);
+    uint32_t w[Chunk<K>::NW] = {};
+    if (nb) load_chunk_edge<K>(s, u, nb, m, w);
+    return any_wrong<K>(load_bytes<true>(s.src + 16 * u, m), load_bytes<true>(s.dst + 16 * u, m), w, nb, m);
 }
 
 // A block covers 512 vectors per pass, two per thread (vectors v and v + 256
@@ -160,8 +152,7 @@ __global__ void __launch_bounds__(256) lsb_verify_kernel(Span s, unsigned long l
 
 // Embed and check one vector u of the span (any class).  A fast vector is
 // embedded in registers, stored, and its stored value is checked against
-// the stream through extraction; an edge vector is embedded byte by byte
-// and each byte this thread wrote is read back.
+// the stream through extraction; an edge vector likewise, masked.
 template <int K>
 __device__ __forceinline__ uint32_t embed_verify_one(const Span &s, const Ranges &r, uintptr_t body_base,
                                                      uint64_t u) {
@@ -178,14 +169,12 @@ __device__ __forceinline__ uint32_t embed_verify_one(const Span &s, const Ranges
         if (!s.inplace) store16<true>(s.dst + 16 * u, load16<true>(s.src + 16 * u));
         return 0;
     }
-    uint32_t bad = 0;
-    const uint64_t t_end = 16 * u + 16 < s.n ? 16 * u + 16 : s.n;
-    for (uint64_t t = 16 * u; t < t_end; ++t) {
-        const uint32_t c = s.src[t];
-        embed_byte<K>(s, t);
-        bad += byte_wrong(s, t, c, s.dst[t]);
-    }
-    return bad;
+    const uint32_t nb = vector_bits<K>(s, u), m = vector_bytes(s, u);
+    if (nb == 0 && s.inplace) return 0;
+    u32x4 c;
+    uint32_t w[Chunk<K>::NW];
+    const u32x4 g = embed_any<K, true>(s, u, nb, m, &c, w);
+    return any_wrong<K>(c, g, w, nb, m);
 }
 
 // Embed and check in one launch: s.src = cover, s.dst = stego (may equal

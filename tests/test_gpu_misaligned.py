@@ -48,3 +48,30 @@ def test_plane_offsets(c, off):
     assert_bytes_equal(to_host(out), msg, "plane extract c=%d off=%d" % (c, off))
     assert int(api.sse(to_dev(cover, pad_before=off, pad_after=16), stego).item()) == int(
         ((want.astype(np.int64) - cover) ** 2).sum())
+
+
+@pytest.mark.parametrize("k", range(1, 9))
+@pytest.mark.parametrize("inplace", [False, True])
+def test_edge_vectors(k, inplace):
+    """Covers of 1..49 bytes with streams that end in every place of their
+    vectors (every partial last field), whole-byte and bit-shifted starts:
+    only edge vectors, against the oracle, with the bytes around untouched."""
+    for n in list(range(1, 34)) + [47, 48, 49]:
+        for t0 in (0, 3, 8):
+            for bits in sorted({0, k * t0, k * t0 + 1, k * (t0 + n) - k - 1, k * (t0 + n) - 1, k * (t0 + n),
+                                k * (t0 + n) + 9}):
+                if bits < 0:
+                    continue
+                need = api._slice_stream_end(k, t0, n, bits)
+                cover = inputs.random_bytes(n, 2705, k, n, t0)
+                stream = inputs.random_bytes(max(need, 1), 2706, k, n, bits)
+                rc, want = oracle.embed_raw(cover, t0, np.concatenate([stream, np.zeros(4, np.uint8)]), bits, k)
+                assert rc == oracle.OK
+                big = to_dev(np.concatenate([np.full(16, 0x77, np.uint8), cover, np.full(16, 0x77, np.uint8)]))
+                view = big[16:16 + n]
+                src = view if inplace else to_dev(cover)
+                api.embed_raw(src, t0, to_dev(stream), bits, k, out=view)
+                got = to_host(big)
+                tag = "k=%d n=%d t0=%d bits=%d" % (k, n, t0, bits)
+                assert_bytes_equal(got[16:16 + n], want, tag)
+                assert (got[:16] == 0x77).all() and (got[16 + n:] == 0x77).all(), tag
