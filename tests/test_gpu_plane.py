@@ -126,3 +126,15 @@ def test_psnr_of_a_single_plane_embed():
     assert abs(p8 - oracle.psnr(sse_dev, pixels)) < 1e-9
     # uniform low bits: mean squared change per field (4^k - 1)/6 = 2.5 at k = 2
     assert abs(sse_dev / pixels - 2.5) < 0.05
+
+
+@pytest.mark.parametrize("n", [0, 1, 15, 16, 17, 511 * 16, 512 * 16 * 4, 512 * 16 * 4 + 5, 256 * 512 * 16 * 4 - 16,
+                               256 * 512 * 16 * 4 + 16 * 513 + 9])
+def test_sse_passes(n):
+    """Sizes around a vector, a block's pass and the whole grid's pass, with
+    the largest differences (every byte 255 apart) and random ones."""
+    a = inputs.random_bytes(n, 2811, n)
+    for b in (inputs.random_bytes(n, 2812, n), np.zeros(n, np.uint8)):
+        for x in (a, np.full(n, 255, np.uint8)):
+            got = int(api.sse(to_dev(x), to_dev(b)).item())
+            assert got == int(((x.astype(np.int64) - b) ** 2).sum())
