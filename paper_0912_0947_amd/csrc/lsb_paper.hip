@@ -5,46 +5,17 @@
 // pair i of data byte j in plane pixel L*i + j of its row.
 //
 // The paper runs this as 4 blocks of at most 32 threads per row, one MEX call
-// per row.  Here one launch covers the whole image: the embed kernel streams
+// per row.  Here one launch covers the whole image: the embed kernels stream
 // every cover byte once (16 bytes per lane, copy plus in-plane update) and
-// the extract kernel gives each data byte one lane that gathers its four
-// pixels, so each output byte has a single writer (the paper's four blocks
-// OR into the same byte).
+// the extract kernels give each run of data bytes one lane that reads its
+// four runs of pixels, so each output byte has a single writer (the paper's
+// four blocks OR into the same byte).
 #include <hip/hip_ext.h>
 
 #include "lsb_host.hpp"
 #include "lsb_paper_device.hpp"
 
-namespace lsb {
-
-// One block per row; dynamic LDS holds the row's data chunk.  C > 0 fixes
-// the channel count at compile time (1, 3, 4), 0 reads it from the span.
-template <int C>
-__global__ void __launch_bounds__(256) lsb_paper_embed_rows_kernel(PaperSpan p) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t paper_chunk[];
-    const PaperRow r = paper_row(p, blockIdx.x);
-    if (r.L == 0) {
-        if (!p.inplace) paper_row_copy(p, r, threadIdx.x, blockDim.x);
-        return;
-    }
-    paper_row_stage(p, r, paper_chunk + kPaperGuard, threadIdx.x, blockDim.x);
-    __syncthreads();
-    if constexpr (C == 1 || C == 3 || C == 4) {
-        if (r.L >= PaperWindow<C>::len) {
-            paper_row_update<C, true>(p, r, paper_chunk, threadIdx.x, blockDim.x);
-            return;
-        }
-    }
-    paper_row_update<C, false>(p, r, paper_chunk, threadIdx.x, blockDim.x);
-}
-
-}  // namespace lsb
-
 using namespace lsb;
-
-// Largest data chunk per row staged in LDS by the row kernel.
-static constexpr uint64_t kPaperRowChunkMax = 60 * 1024;
-static_assert(paper_row_lds_bytes(kPaperRowChunkMax) <= 64 * 1024, "row kernel LDS within 64 KiB");
 
 static int paper_check(uint32_t h, uint32_t w, uint32_t c, uint32_t plane, uint64_t len, const char *who) {
     if (c == 0 || plane >= c) return fail(LSB_E_ARG, "%s: plane %u outside 0..%u", who, plane, c ? c - 1 : 0);
@@ -54,6 +25,52 @@ static int paper_check(uint32_t h, uint32_t w, uint32_t c, uint32_t plane, uint6
         return fail(LSB_E_CAPACITY, "%s: %llu data bytes exceed the capacity h*floor(w/4) = %llu", who,
                     (unsigned long long)len, (unsigned long long)cap);
     return LSB_OK;
+}
+
+typedef void (*RowFn)(PaperSpan, RowMap, uint64_t);
+
+// Run a unit kernel over n_rows rows of `units` units, `unr` units per
+// thread: short rows share blocks of 256 threads, long ones are cut into equal
+// shares of at most 512 units (1024 for rows that one block takes whole).
+// False, nothing launched, if the grid would pass the limits of a launch
+// (images of tens of gigabytes: the grid-stride kernels take them).
+static bool launch_rows(const RowFn fn[2], const PaperSpan &p, uint64_t units, uint64_t n_rows, uint32_t unr,
+                        hipStream_t stream) {
+    if (units > (1u << 28)) return false;
+    RowMap m{(uint32_t)units, 1, 1, (uint32_t)units, 0};
+    uint64_t per_block = units;
+    if (2 * units <= 256 * unr) {
+        m.rows = 256 * unr / (uint32_t)units;
+        m.magic = (uint32_t)(((1u << 20) + units - 1) / units);
+        per_block = m.rows * units;
+    } else if (units > 1024) {
+        m.blocks = (uint32_t)ceil_div(units, 512);
+        m.share = (uint32_t)ceil_div(units, m.blocks);
+        per_block = m.share;
+    }
+    const uint64_t block = ceil_div(ceil_div(per_block, unr), 64) * 64;
+    const uint64_t blocks = ceil_div(n_rows, m.rows) * m.blocks;
+    if (blocks * block > 0xFFFFFFFFull || blocks > 0x7FFFFFFFull) return false;
+    hipEvent_t e0, e1;
+    take_launch_events(&e0, &e1);
+    hipExtLaunchKernelGGL(fn[m.rows > 1], dim3((unsigned)blocks), dim3((unsigned)block), 0, stream, e0, e1, 0, p, m,
+                          n_rows);
+    return true;
+}
+
+template <int C>
+struct PaperRows {
+    static constexpr RowFn embed[2] = {lsb_paper_embed_units_kernel<C, false>, lsb_paper_embed_units_kernel<C, true>};
+};
+template <int C>
+struct PaperRowsX {
+    static constexpr RowFn extract[2] = {lsb_paper_extract_units_kernel<C, false>,
+                                         lsb_paper_extract_units_kernel<C, true>};
+};
+
+static int launched(const char *what) {
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? LSB_OK : hip_fail(e, what);
 }
 
 extern "C" {
@@ -85,24 +102,16 @@ int lsb_paper_embed(const uint8_t *cover, uint8_t *stego, uint32_t h, uint32_t w
     p.q = w / 4;
     p.inplace = cover == stego;
     if (p.rowbytes >= (1ull << 31)) return fail(LSB_E_ARG, "lsb_paper_embed: rows of 2^31 bytes or more");
-    const bool aligned = (((uintptr_t)cover | (uintptr_t)stego) & 15u) == 0;
-    if (aligned && p.rowbytes % 16 == 0 && p.q + 4 <= kPaperRowChunkMax && h < (1u << 31)) {
-        // rows past the last data-carrying one: copied out-of-place, untouched in-place
-        const uint64_t rows_with_data = p.q ? ceil_div(len, p.q) : 0;
-        const uint64_t rows = p.inplace ? rows_with_data : h;
-        if (rows == 0) return LSB_OK;
-        const size_t lds = (size_t)paper_row_lds_bytes(p.q);
-        hipEvent_t e0, e1;
-        take_launch_events(&e0, &e1);
-        void (*fn)(PaperSpan) = c == 1 ? lsb_paper_embed_rows_kernel<1>
-                                : c == 3 ? lsb_paper_embed_rows_kernel<3>
-                                : c == 4 ? lsb_paper_embed_rows_kernel<4>
-                                         : lsb_paper_embed_rows_kernel<0>;
-        hipExtLaunchKernelGGL(fn, dim3((unsigned)rows), dim3(256), lds, (hipStream_t)stream, e0, e1, 0, p);
-        const hipError_t e = hipGetLastError();
-        return e == hipSuccess ? LSB_OK : hip_fail(e, "paper row embed kernel launch");
+    // rows past the last data-carrying one: copied out-of-place, untouched in-place
+    const uint64_t rows = p.inplace ? (p.q ? ceil_div(len, p.q) : 0) : h;
+    if (rows == 0) return LSB_OK;
+    const bool vec = p.rowbytes >= 16;
+    if (vec && (c == 1 || c == 3 || c == 4)) {
+        // vectors from 16-byte addresses on, plus the partial ones at a row's two ends
+        const uint64_t units = ceil_div(p.rowbytes + (p.rowbytes % 16 ? 15 : (uintptr_t)stego % 16), 16);
+        const RowFn *fn = c == 1 ? PaperRows<1>::embed : (c == 3 ? PaperRows<3>::embed : PaperRows<4>::embed);
+        if (launch_rows(fn, p, units, rows, 2, (hipStream_t)stream)) return launched("paper embed kernel launch");
     }
-    const bool vec = aligned && p.rowbytes >= 16;
     const uint64_t items = vec ? ceil_div(n, 16) : n;
     uint64_t blocks = ceil_div(items, 256);
     const uint64_t cap = (uint64_t)device_cus() * 16;
@@ -115,8 +124,7 @@ int lsb_paper_embed(const uint8_t *cover, uint8_t *stego, uint32_t h, uint32_t w
     else
         hipExtLaunchKernelGGL(lsb_paper_embed_kernel<false>, dim3((unsigned)blocks), dim3(256), 0,
                               (hipStream_t)stream, e0, e1, 0, p);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? LSB_OK : hip_fail(e, "paper embed kernel launch");
+    return launched("paper embed kernel launch");
 }
 
 int lsb_paper_extract(const uint8_t *stego, uint32_t h, uint32_t w, uint32_t c, uint32_t plane, uint8_t *data_out,
@@ -138,6 +146,15 @@ int lsb_paper_extract(const uint8_t *stego, uint32_t h, uint32_t w, uint32_t c, 
     p.c = c;
     p.plane = plane;
     p.q = w / 4;
+    if (c <= 4) {
+        const uint64_t units = ceil_div(p.q < len ? p.q : len, c == 1 ? 16 : 4);
+        const RowFn *fn = c == 1   ? PaperRowsX<1>::extract
+                          : c == 2 ? PaperRowsX<2>::extract
+                          : c == 3 ? PaperRowsX<3>::extract
+                                   : PaperRowsX<4>::extract;
+        if (launch_rows(fn, p, units, ceil_div(len, p.q), 1, (hipStream_t)stream))
+            return launched("paper extract kernel launch");
+    }
     uint64_t blocks = ceil_div(len, 256);
     const uint64_t cap = (uint64_t)device_cus() * 16;
     if (blocks > cap) blocks = cap;
@@ -145,8 +162,7 @@ int lsb_paper_extract(const uint8_t *stego, uint32_t h, uint32_t w, uint32_t c, 
     take_launch_events(&e0, &e1);
     hipExtLaunchKernelGGL(lsb_paper_extract_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, e0,
                           e1, 0, p);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? LSB_OK : hip_fail(e, "paper extract kernel launch");
+    return launched("paper extract kernel launch");
 }
 
 }  // extern "C"

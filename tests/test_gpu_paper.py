@@ -117,3 +117,34 @@ def test_errors():
     with pytest.raises(LsbError) as ei:
         api.paper_extract(buf, 8, 8, 3, 0, 17)
     assert ei.value.code == E_CAPACITY
+
+
+@pytest.mark.parametrize("c", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("w", [4, 5, 6, 16, 17, 23, 43, 64, 85, 127, 171, 341, 342, 1365, 1366, 2731, 5463, 9001, 16411])
+def test_row_units(w, c):
+    """Widths around a vector, a run of data bytes, rows that share a block,
+    rows of one block and rows of several, with image pointers off a 16-byte
+    boundary; full capacity, a short last row (down to one byte) and in
+    place."""
+    h = 5 if w > 600 else 37
+    cap = oracle.paper_capacity(h, w)
+    cover = inputs.random_bytes(h * w * c, 1351, w, c)
+    for t, ln in enumerate(sorted({cap, cap - w // 8, (h - 1) * (w // 4) + 1, w // 4 + 1, 3, 0})):
+        if not 0 <= ln <= cap:
+            continue
+        plane, off = (w + t) % c, (5 * t + w) % 16
+        data = inputs.random_bytes(ln, 1352, w, c, t)
+        rc, want = oracle.paper_embed(cover, h, w, c, plane, data)
+        assert rc == 0
+        tag = "w=%d c=%d plane=%d len=%d off=%d" % (w, c, plane, ln, off)
+        big = to_dev(np.full(cover.size + 48, 0x77, np.uint8))
+        st = big[16 + off:16 + off + cover.size]
+        api.paper_embed(to_dev(cover, pad_before=t, pad_after=16), h, w, c, plane, to_dev(data, pad_before=t), out=st)
+        got = to_host(big)
+        assert_bytes_equal(got[16 + off:16 + off + cover.size], want, "embed " + tag)
+        assert (got[:16 + off] == 0x77).all() and (got[16 + off + cover.size:] == 0x77).all(), tag
+        out = empty_dev(ln, pad_before=off)
+        assert_bytes_equal(to_host(api.paper_extract(st, h, w, c, plane, ln, out=out)), data, "extract " + tag)
+        buf = to_dev(cover, pad_before=off, pad_after=16)
+        api.paper_embed(buf, h, w, c, plane, to_dev(data), out=buf)
+        assert_bytes_equal(to_host(buf), want, "in place " + tag)
