@@ -4,14 +4,16 @@
 // Section VI step 2 / Section VII step 2 separate one plane of the image
 // before embedding.  Here the fields are the bytes of plane `plane` of an
 // HWC image (byte p*c + plane for pixel p), in raster order; the stream, bit
-// order, header and partial last field are those of lsb_embed.  Out of
-// place, a vector copy kernel first copies the cover, then a strided kernel
-// rewrites the plane bytes that carry stream bits.
+// order, header and partial last field are those of lsb_embed.  Images of up
+// to 4 channels take one pass over their vectors; others a vector copy (out of
+// place), then a strided kernel over the plane bytes that carry stream bits.
 //
 // Section VIII reports PSNR = 10*log10(255^2 / MSE).  lsb_sse sums the
 // squared byte differences of two buffers on the device (16 bytes per lane,
 // block reduction, one 64-bit atomic per block).
 #include <hip/hip_ext.h>
+
+#include <algorithm>
 
 #include "lsb_host.hpp"
 
@@ -90,7 +92,7 @@ __global__ void __launch_bounds__(kSseBlock) lsb_sse_kernel(const uint8_t *a, co
     }
 }
 
-typedef void (*PlaneEmbedFn)(Span, uint32_t);
+typedef void (*PlaneEmbedFn)(Span, uint32_t, uint64_t, uint64_t);
 typedef void (*PlaneExtractFn)(Span, uint32_t, uint64_t, uint32_t *, int32_t *);
 
 template <int K>
@@ -130,11 +132,10 @@ static PlaneExtractFn plane_extract_fn(int k, uint32_t c) {
     }
 }
 
-// Grid of the plane kernels: a thread per item.  They are grid-stride
-// loops, and a looping wave's wait for its next loads also waits for its
-// previous stores; capped at 16 blocks per CU, the plane embed of an
-// 8192x8192x3 image took 70-72 us against 66-67 us uncapped (extract
-// 37.8-38.2 against 37.3-37.6 us).
+// Grid of the strided and extract kernels: a thread per item.  They are
+// grid-stride loops, and a looping wave's wait for its next loads also waits
+// for its previous stores; capped at 16 blocks per CU, the extract of an
+// 8192x8192x3 image took 37.8-38.2 us against 37.3-37.6 us uncapped.
 static unsigned grid_cap(uint64_t items) {
     const uint64_t blocks = ceil_div(items ? items : 1, 256);
     return (unsigned)(blocks < (uint64_t)INT32_MAX ? blocks : (uint64_t)INT32_MAX);
@@ -165,7 +166,7 @@ int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels, uint3
     hipStream_t st = (hipStream_t)stream;
     if (c == 1) return lsb_embed(cover, stego, pixels, msg, len, k, stream);  // the plane is the image
     if (c <= 4) {
-        // one pass: each lane moves 16 pixels (c vectors) and rewrites their plane bytes
+        // one pass over the image's vectors
         Span s{};
         s.src = cover;
         s.dst = stego;
@@ -176,11 +177,14 @@ int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels, uint3
         s.hdr_len = 4;
         s.k = k;
         s.inplace = cover == stego;
-        const Ranges r = embed_ranges(s);
-        if (!r.count) return LSB_OK;
+        // in place: up to the last vector that carries stream bits
+        const uint64_t fields = ceil_div(s.bits, (uint64_t)k);
+        const uint64_t count = ceil_div(s.inplace && fields < pixels ? fields * c : n, 16);
+        const uint64_t blocks = std::min<uint64_t>(ceil_div(count, 512), 0xFFFFFFFFull / 256);
         hipEvent_t e0, e1;
         take_launch_events(&e0, &e1);
-        hipExtLaunchKernelGGL(plane_embed_fn(k, c), dim3(grid_cap(r.count)), dim3(256), 0, st, e0, e1, 0, s, plane);
+        hipExtLaunchKernelGGL(plane_embed_fn(k, c), dim3((unsigned)blocks), dim3(256), 0, st, e0, e1, 0, s, plane, n,
+                              count);
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? LSB_OK : hip_fail(e, "plane embed kernel launch");
     }

@@ -138,3 +138,30 @@ def test_sse_passes(n):
         for x in (a, np.full(n, 255, np.uint8)):
             got = int(api.sse(to_dev(x), to_dev(b)).item())
             assert got == int(((x.astype(np.int64) - b) ** 2).sum())
+
+
+@pytest.mark.parametrize("k", range(1, 9))
+@pytest.mark.parametrize("c", [2, 3, 4])
+def test_plane_vectors(k, c):
+    """The embed's 16-byte vectors: images from one vector to several
+    512-vector blocks, messages that end in every place of a vector, each
+    plane, with the bytes around untouched; in place likewise."""
+    for pixels in (40, 43, 171, 1366, 2731, 2732, 9001):
+        cap = oracle.capacity(pixels, k)
+        for ln in sorted({0, 1, 5, cap // 3, cap - 7, cap - 3, cap - 1, cap}):
+            if not 0 <= ln <= cap:
+                continue
+            plane, off = (ln + pixels) % c, (ln + k) % 16
+            cover = inputs.random_bytes(pixels * c, 2821, k, c, pixels)
+            msg = inputs.random_bytes(ln, 2822, k, c, ln)
+            rc, want = oracle.embed_plane(cover, c, plane, msg, k)
+            assert rc == OK
+            tag = "k=%d c=%d plane=%d pixels=%d len=%d" % (k, c, plane, pixels, ln)
+            for src in (to_dev(cover), None):
+                big = to_dev(np.concatenate([np.full(16, 0x77, np.uint8), cover, np.full(16, 0x77, np.uint8)]),
+                             pad_before=off)
+                view = big[16:16 + cover.size]
+                api.embed_plane(view if src is None else src, c, plane, to_dev(msg, pad_before=ln % 5), k, out=view)
+                got = to_host(big)
+                assert_bytes_equal(got[16:16 + cover.size], want, tag)
+                assert (got[:16] == 0x77).all() and (got[16 + cover.size:] == 0x77).all(), tag
