@@ -152,6 +152,7 @@ _CHECKED = {_U64: _range_checked(_U64, 64, False), _I64: _range_checked(_I64, 64
 
 _lock = threading.Lock()
 _lib = None
+_bind = None
 
 
 class LsbError(RuntimeError):
@@ -177,8 +178,31 @@ def lib():
                     fn.argtypes = [_CHECKED.get(a, a) for a in args]
                 from . import tune
                 tune.load(handle)  # stored launch configurations, if any
+                _install(handle)
                 _lib = handle
     return _lib
+
+
+def _install(handle) -> None:
+    """Point the native marshalling module at the loaded library."""
+    global _bind
+    import torch  # noqa: F401  (its libraries, which the module links)
+    try:
+        from . import _bind as module
+    except ImportError as e:
+        raise RuntimeError("the _bind module is not built or does not load (%s); run "
+                           "`python -m paper_0912_0947_amd.build`" % e) from e
+    module.install(handle._handle)
+    _bind = module
+
+
+def bind():
+    """The native marshalling module over the loaded library: its functions
+    return the library's code, or None for arguments that are not the
+    ordinary case (the caller then takes its checked path)."""
+    if _lib is None:
+        lib()
+    return _bind
 
 
 def check(rc: int) -> int:

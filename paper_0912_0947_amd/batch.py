@@ -7,7 +7,7 @@ import ctypes
 import numpy as np
 import torch
 
-from ._lib import JOB_RAW, OP_EMBED, OP_EXTRACT, OP_MIXED, STATIC_MAX_JOBS, Job, LaunchCfg, check, lib
+from ._lib import JOB_RAW, OP_EMBED, OP_EXTRACT, OP_MIXED, STATIC_MAX_JOBS, Job, LaunchCfg, bind, check, lib
 
 ALIGN = 256
 
@@ -106,6 +106,11 @@ class Plan:
 
     def embed_batch(self, cover_arena, stego_arena, msg_arena, status_dev, stream=None) -> None:
         """lsb_embed_batch: every job of the plan must be an embed."""
+        rc = bind().embed_batch(self._p.value, self.n_jobs, *self._need, cover_arena, stego_arena, msg_arena,
+                                status_dev, None if stream is None else stream.cuda_stream)
+        if rc is not None:
+            check(rc)
+            return
         if stream is None:
             stream = torch.cuda.current_stream()
         c, st, m = self._need
@@ -115,6 +120,11 @@ class Plan:
 
     def extract_batch(self, stego_arena, msg_arena, len_dev, status_dev, stream=None) -> None:
         """lsb_extract_batch: every job of the plan must be an extract."""
+        rc = bind().extract_batch(self._p.value, self.n_jobs, *self._need[1:], stego_arena, msg_arena, len_dev,
+                                  status_dev, None if stream is None else stream.cuda_stream)
+        if rc is not None:
+            check(rc)
+            return
         if stream is None:
             stream = torch.cuda.current_stream()
         _, st, m = self._need
@@ -128,6 +138,11 @@ class Plan:
         return int(check(lib().lsb_plan_tiles(self._p)))
 
     def run(self, cover_arena, stego_arena, msg_arena, len_dev, status_dev, stream=None) -> None:
+        rc = bind().plan_run(self._p.value, self.n_jobs, *self._need, cover_arena, stego_arena, msg_arena, len_dev,
+                             status_dev, None if stream is None else stream.cuda_stream)
+        if rc is not None:
+            check(rc)
+            return
         if stream is None:
             stream = torch.cuda.current_stream()
         c, st, m = self._need

@@ -1,7 +1,8 @@
-"""Build liblsb.so (all HIP sources, gfx950) in-tree with hipcc.
+"""Build liblsb.so (all HIP sources, gfx950) and the Python layer's native
+marshalling module ``_bind.so`` in-tree with hipcc.
 
 Usage: ``python -m paper_0912_0947_amd.build`` or ``build()`` from Python.
-The library lands next to this file as ``liblsb.so``.
+Both land next to this file.
 """
 from __future__ import annotations
 
@@ -16,6 +17,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblsb.so")
+BIND = os.path.join(HERE, "_bind.so")
+BIND_SOURCE = os.path.join(CSRC, "bind", "lsb_bind.cpp")
 ARCH = os.environ.get("LSB_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [
@@ -43,13 +46,33 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found: the HIP library cannot be built")
 
 
+def bind_command(out: str) -> list[str]:
+    """Command that builds the marshalling module against this Python and
+    its torch (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    dirs = [sysconfig.get_paths()["include"], *cpp_extension.include_paths(), os.path.join(ROOT, "include")]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+            "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+            *[x for d in dirs for x in ("-isystem", d)], "-isystem", os.path.join(os.path.dirname(ROCM_LIB), "include"),
+            BIND_SOURCE, "-o", out, "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            "-Wl,-rpath," + libs]
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
-    """Compile every source to an object (in parallel), then link liblsb.so."""
+    """Compile every source to an object (in parallel), then link liblsb.so;
+    the marshalling module builds beside them."""
     hipcc = _hipcc()
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     t0 = time.time()
-    procs = []
+    bind_tmp = BIND + ".tmp%d" % os.getpid()
+    procs = [(BIND_SOURCE, subprocess.Popen(bind_command(bind_tmp), stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                                            text=True))]
     objs = []
     for src in sources():
         obj = os.path.join(objdir, os.path.basename(src) + ".o")
@@ -73,6 +96,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp, *objs, *LINK_FLAGS])
     os.replace(tmp, LIB)
+    os.replace(bind_tmp, BIND)
     if verbose:
         print("built %s in %.1f s" % (LIB, time.time() - t0), flush=True)
     return LIB
