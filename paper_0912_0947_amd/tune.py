@@ -1,5 +1,6 @@
-"""Autotuning driver: runs lsb_autotune over (op, k, size) points and the
-batched-kernel sweep, and stores the winners as JSON next to this file.
+"""Autotuning driver: chooses launch shapes per (op, k, size) in embed/extract
+pairs, the large-image workload's in its own sequence, sweeps the batched
+kernel, and stores the winners as JSON next to this file.
 
 ``load()`` installs a stored table into the library (called on import of
 paper_0912_0947_amd.api).  Buckets that were not tuned take the entry of the
@@ -17,12 +18,12 @@ import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "tune_gfx950.json")
-SIZES = [1 << 12, 1 << 14, 1 << 16, 1 << 18, 786432, 1 << 21, 6220800, 1 << 24, 1 << 26, 201326592, 1 << 29]
+# One size per bucket, in its middle or the size of a workload that falls into it.
+SIZES = [{19: 786432, 22: 6220800, 27: 201326592}.get(b, 3 << (b - 1)) for b in range(12, 31)]
 KS = range(1, 9)
-# Sizes from here up are timed in steady state over rotating buffer sets
-# (their working set exceeds the 256 MB last-level cache); smaller ones by
-# lsb_autotune after a cache flush.
-ROTATE_MIN = 1 << 26
+# Buffers from here up take streaming (non-temporal) shapes only: one cover
+# and its stego no longer fit the 256 MB last-level cache.
+STREAM_MIN = 1 << 27
 ROT_SETS = 3
 BLOCKS, UNROLLS, CAPS, ORDERS = (256, 512, 1024), (1, 2, 4), (0, 1, 2, 4, 8, 16), (0, 1)
 
@@ -72,20 +73,17 @@ def load(handle=None, path: str = TABLE) -> bool:
     return True
 
 
-def tune_rotating(op: int, k: int, n: int, sets, reps: int = 9):
-    """Steady-state choice for one (op, k, n).  Each repetition launches every
-    candidate shape once, in turn, over the buffer sets (round-robin, so slow
-    drift of the device during the sweep affects all candidates alike); each
-    launch is timed by events bound to the kernel itself.  The lowest median
-    wins and is installed for n's bucket.  Returns (cfg, median us, the next
-    best three as (cfg, us)).  ``sets`` holds (cover, stego, msg, out,
-    len_status) per set; every stego already carries a full-capacity stream.
-
-    Buffers beyond the last-level cache get streaming (non-temporal) shapes
-    only: cached stores cannot be reused at these sizes, they only leave dirty
-    lines that the next kernel has to write back (a k = 4 extract with cached
-    stores measured faster alone but slowed itself and the embed after it by
-    about 6 % in the embed/extract sequence)."""
+def tune_pair(k: int, n: int, sets, reps: int = 4, finals: int = 12, log=print):
+    """Shapes of embed and extract for (k, n), chosen together: each candidate
+    of one operation is timed in passes that embed into a stego buffer and
+    extract from it, over the buffer sets in turn, with the other operation at
+    its best shape so far.  The score is the sum of both launches (each timed
+    by events bound to its kernel), so a shape that leaves the memory system
+    in a state the next kernel pays for, or its output in the caches, is
+    charged or credited for it.  Candidates take turns (slow drift of the
+    device affects all alike); the best ``finals`` are timed again, four times
+    as often.  ``sets`` holds (cover, stego, msg, out, len_status) per set.
+    Returns the two table entries."""
     import statistics
 
     import torch
@@ -95,36 +93,58 @@ def tune_rotating(op: int, k: int, n: int, sets, reps: int = 9):
 
     L = lib()
     cap = api.capacity(n, k)
-    packs = (0, 1) if (op == api.OP_EXTRACT and k == 1) else (0,)
-    cands = [{"block": b, "unroll": u, "blocks_per_cu": c, "nontemporal": 1, "pack": pk, "order": o}
-             for o in ORDERS for pk in packs for b in BLOCKS for u in UNROLLS for c in CAPS]
-    times = [[] for _ in cands]
-    ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in cands]
-    for e0, e1 in ev:  # create the HIP events (torch records lazily); the library re-records them
-        e0.record()
-        e1.record()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    for e in ev:  # create the HIP events (torch records lazily); the library re-records them
+        e.record()
     torch.cuda.synchronize()
-    it = 0
-    for r in range(reps + 1):
-        for ci, c in enumerate(cands):
-            api.tune_set(op, k, bucket(n), c["block"], c["unroll"], c["blocks_per_cu"], c["nontemporal"], c["pack"],
-                         c["order"])
-            cover, stego, msg, out, ls = sets[it % len(sets)]
-            it += 1
-            e0, e1 = ev[ci]
-            L.lsb_time_next_launch(e0, e1)
-            if op == api.OP_EMBED:
-                api.embed(cover[:n], msg[:cap], k, out=stego[:n])
-            else:
-                api.extract(stego[:n], k, out=out[:cap], len_status=ls)
-            torch.cuda.synchronize()
-            if r:  # repetition 0 warms every shape up
-                times[ci].append(e0.elapsed_time(e1))
-    med = sorted((statistics.median(t) * 1e3, ci) for ci, t in enumerate(times))
-    best = cands[med[0][1]]
-    api.tune_set(op, k, bucket(n), best["block"], best["unroll"], best["blocks_per_cu"], best["nontemporal"],
-                 best["pack"], best["order"])
-    return best, med[0][0], [(cands[ci], round(us, 2)) for us, ci in med[1:4]]
+    best = {op: {"block": 256, "unroll": 2, "blocks_per_cu": 0, "nontemporal": 1, "pack": 0, "order": 0}
+            for op in (api.OP_EMBED, api.OP_EXTRACT)}
+    it = [0]
+
+    def install(op, c):
+        api.tune_set(op, k, bucket(n), c["block"], c["unroll"], c["blocks_per_cu"], c["nontemporal"], c["pack"],
+                     c["order"])
+
+    def one_pass():
+        cover, stego, msg, out, ls = sets[it[0] % len(sets)]
+        it[0] += 1
+        L.lsb_time_next_launch(ev[0], ev[1])
+        api.embed(cover[:n], msg[:cap], k, out=stego[:n])
+        L.lsb_time_next_launch(ev[2], ev[3])
+        api.extract(stego[:n], k, out=out[:cap], len_status=ls)
+        torch.cuda.synchronize()
+        return ev[0].elapsed_time(ev[1]) * 1e3, ev[2].elapsed_time(ev[3]) * 1e3
+
+    def rank(op, cands, rounds):
+        times = [[] for _ in cands]
+        for r in range(rounds + 1):
+            for ci, c in enumerate(cands):
+                install(op, c)
+                t = one_pass()
+                if r:  # round 0 warms every shape up
+                    times[ci].append(t)
+        med = [(statistics.median(e + x for e, x in ts), ci) for ci, ts in enumerate(times)]
+        return sorted(med), times
+
+    entries = {}
+    nts = (1,) if n >= STREAM_MIN else (0, 1)
+    for op in (api.OP_EXTRACT, api.OP_EMBED, api.OP_EXTRACT):
+        for o in best:
+            install(o, best[o])
+        packs = (0, 1) if (op == api.OP_EXTRACT and k == 1) else (0,)
+        cands = [{"block": b, "unroll": u, "blocks_per_cu": c, "nontemporal": nt, "pack": pk, "order": o}
+                 for nt in nts for o in ORDERS for pk in packs for b in BLOCKS for u in UNROLLS for c in CAPS]
+        order, _ = rank(op, cands, reps)
+        cands = [cands[ci] for _, ci in order[:finals]]
+        order, times = rank(op, cands, 4 * reps)
+        best[op] = cands[order[0][1]]
+        install(op, best[op])
+        us = statistics.median(t[op] for t in times[order[0][1]])
+        entries[op] = {"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": best[op], "us": round(us, 2),
+                       "method": "pair"}
+    log("k=%d n=%d -> embed %s %.1f us, extract %s %.1f us" % (
+        k, n, best[0], entries[0]["us"], best[1], entries[1]["us"]))
+    return [entries[0], entries[1]]
 
 
 # The large-image workload: embed then extract at k = 1, 2, 4 on one 8192 x
@@ -138,10 +158,9 @@ def tune_sequence(n: int = SEQUENCE_N, seq=SEQUENCE, reps: int = 7, log=print):
     sequence.  For each member (op, k) in turn every streaming candidate shape
     is installed for n's bucket and the whole sequence runs reps + 1 times
     over three rotating buffer sets, the member's launch timed by events bound
-    to it; the lowest median wins before the next member is tuned.  Same-op
-    rotation ranks near-equal shapes by noise: in this sequence the preceding
-    kernels' traffic separates them (one shape that tied in rotation ran 10 %
-    slower here).  Returns table entries."""
+    to it; the lowest median wins before the next member is tuned.
+    Shapes that tie on an idle device can differ by 10 % here, behind the
+    preceding kernels' traffic.  Returns table entries."""
     import statistics
 
     import torch
@@ -215,57 +234,28 @@ def tune_sequence(n: int = SEQUENCE_N, seq=SEQUENCE, reps: int = 7, log=print):
     return entries
 
 
-def tune_plain(reps: int = 5, sizes=SIZES, ks=KS, log=print):
+def tune_plain(reps: int = 4, sizes=SIZES, ks=KS, log=print):
     import torch
 
     from . import api, inputs
 
     dev = torch.device("cuda:0")
     entries = []
-    small = [n for n in sizes if n < ROTATE_MIN]
-    large = [n for n in sizes if n >= ROTATE_MIN]
-    if small:
-        biggest = max(small)
+    biggest = max(sizes)
+    sets = []
+    for j in range(ROT_SETS):
         cover = torch.empty(biggest, dtype=torch.uint8, device=dev)
-        stego = torch.empty(biggest, dtype=torch.uint8, device=dev)
         msg = torch.empty(biggest, dtype=torch.uint8, device=dev)
-        inputs.fill_uniform(cover, 11)
-        inputs.fill_uniform(msg, 12)
-        for n in small:
-            for k in ks:
-                cap = api.capacity(n, k)
-                for op in (api.OP_EMBED, api.OP_EXTRACT):
-                    cfg, us = api.autotune(op, k, cover[:n], stego[:n], msg[:cap], reps=reps)
-                    entries.append({"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": cfg, "us": round(us, 2),
-                                    "method": "flush"})
-                    log("op=%d k=%d n=%d -> %s %.1f us" % (op, k, n, cfg, us))
-        del cover, stego, msg
-    if large:
-        biggest = max(large)
-        sets = []
-        for j in range(ROT_SETS):
-            cover = torch.empty(biggest, dtype=torch.uint8, device=dev)
-            msg = torch.empty(biggest, dtype=torch.uint8, device=dev)
-            inputs.fill_uniform(cover, 13 + j)
-            inputs.fill_uniform(msg, 23 + j)
-            sets.append((cover, torch.empty(biggest, dtype=torch.uint8, device=dev), msg,
-                         torch.empty(biggest, dtype=torch.uint8, device=dev),
-                         torch.zeros(2, dtype=torch.int32, device=dev)))
-        for n in large:
-            for k in ks:
-                cap = api.capacity(n, k)
-                for cover, stego, msg, _, _ in sets:  # stegos carry full-capacity streams
-                    api.embed(cover[:n], msg[:cap], k, out=stego[:n])
-                for op in (api.OP_EMBED, api.OP_EXTRACT):
-                    cfg, us, runners = tune_rotating(op, k, n, sets, reps=max(reps, 9))
-                    entries.append({"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": cfg, "us": round(us, 2),
-                                    "method": "rotating", "runners_up": runners})
-                    log("op=%d k=%d n=%d -> %s %.1f us (rotating; next %s)" % (op, k, n, cfg, us, runners))
-                # the extracts above must have returned every message
-                for cover, stego, msg, out, ls in sets:
-                    st = ls.cpu().tolist()
-                    assert st == [cap, 0], (op, k, n, st)
-        del sets
+        inputs.fill_uniform(cover, 13 + j)
+        inputs.fill_uniform(msg, 23 + j)
+        sets.append((cover, torch.empty(biggest, dtype=torch.uint8, device=dev), msg,
+                     torch.empty(biggest, dtype=torch.uint8, device=dev),
+                     torch.zeros(2, dtype=torch.int32, device=dev)))
+    for n in sizes:
+        for k in ks:
+            entries += tune_pair(k, n, sets, reps=reps, log=log)
+            for _, _, _, _, ls in sets:  # the extracts returned every message
+                assert ls.cpu().tolist() == [api.capacity(n, k), 0], (k, n, ls.cpu().tolist())
     return entries
 
 
@@ -331,7 +321,7 @@ def tune_batch(log=print, count: int = 4096):
 
 def main():
     ap = argparse.ArgumentParser()
-    ap.add_argument("--reps", type=int, default=5)
+    ap.add_argument("--reps", type=int, default=4)
     ap.add_argument("--batch", action="store_true", help="also sweep the batched kernel")
     ap.add_argument("--batch-only", action="store_true",
                     help="sweep the batched kernel only; the stored plain-kernel entries stay")
