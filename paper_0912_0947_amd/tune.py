@@ -24,6 +24,8 @@ KS = range(1, 9)
 # Buffers from here up take streaming (non-temporal) shapes only: one cover
 # and its stego no longer fit the 256 MB last-level cache.
 STREAM_MIN = 1 << 27
+# Runs of blocks per XCD start at 128 blocks: smaller covers keep launch order.
+RUNS_MIN = 1 << 21
 ROT_SETS = 3
 BLOCKS, UNROLLS, CAPS, ORDERS = (256, 512, 1024), (1, 2, 4), (0, 1, 2, 4, 8, 16), (0, 1)
 
@@ -128,12 +130,13 @@ def tune_pair(k: int, n: int, sets, reps: int = 4, finals: int = 12, log=print):
 
     entries = {}
     nts = (1,) if n >= STREAM_MIN else (0, 1)
+    orders = ORDERS if n >= RUNS_MIN else (0,)
     for op in (api.OP_EXTRACT, api.OP_EMBED, api.OP_EXTRACT):
         for o in best:
             install(o, best[o])
         packs = (0, 1) if (op == api.OP_EXTRACT and k == 1) else (0,)
         cands = [{"block": b, "unroll": u, "blocks_per_cu": c, "nontemporal": nt, "pack": pk, "order": o}
-                 for nt in nts for o in ORDERS for pk in packs for b in BLOCKS for u in UNROLLS for c in CAPS]
+                 for nt in nts for o in orders for pk in packs for b in BLOCKS for u in UNROLLS for c in CAPS]
         order, _ = rank(op, cands, reps)
         cands = [cands[ci] for _, ci in order[:finals]]
         order, times = rank(op, cands, 4 * reps)
