@@ -129,6 +129,9 @@ __device__ __forceinline__ void store16(uint8_t *p, u32x4 v) {
     else *q = v;
 }
 
+// Access kinds of the layout kernels.
+enum Access { CACHED = 0, STREAM_LOADS = 1, STREAM = 2 };
+
 __device__ __forceinline__ uint32_t bswap32(uint32_t x) { return __builtin_bswap32(x); }
 
 // Logical stream byte s (header bytes come from the header value).

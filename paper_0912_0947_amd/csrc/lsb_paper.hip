@@ -58,14 +58,17 @@ static bool launch_rows(const RowFn fn[2], const PaperSpan &p, uint64_t units, u
     return true;
 }
 
+// [access kind][short rows]
 template <int C>
-struct PaperRows {
-    static constexpr RowFn embed[2] = {lsb_paper_embed_units_kernel<C, false>, lsb_paper_embed_units_kernel<C, true>};
+struct PaperEmbed {
+    static constexpr RowFn fn[3][2] = {
+        {lsb_paper_embed_units_kernel<C, false, CACHED>, lsb_paper_embed_units_kernel<C, true, CACHED>},
+        {lsb_paper_embed_units_kernel<C, false, STREAM_LOADS>, lsb_paper_embed_units_kernel<C, true, STREAM_LOADS>},
+        {lsb_paper_embed_units_kernel<C, false, STREAM>, lsb_paper_embed_units_kernel<C, true, STREAM>}};
 };
 template <int C>
-struct PaperRowsX {
-    static constexpr RowFn extract[2] = {lsb_paper_extract_units_kernel<C, false>,
-                                         lsb_paper_extract_units_kernel<C, true>};
+struct PaperExtract {
+    static constexpr RowFn fn[2] = {lsb_paper_extract_units_kernel<C, false>, lsb_paper_extract_units_kernel<C, true>};
 };
 
 static int launched(const char *what) {
@@ -109,7 +112,8 @@ int lsb_paper_embed(const uint8_t *cover, uint8_t *stego, uint32_t h, uint32_t w
     if (vec && (c == 1 || c == 3 || c == 4)) {
         // vectors from 16-byte addresses on, plus the partial ones at a row's two ends
         const uint64_t units = ceil_div(p.rowbytes + (p.rowbytes % 16 ? 15 : (uintptr_t)stego % 16), 16);
-        const RowFn *fn = c == 1 ? PaperRows<1>::embed : (c == 3 ? PaperRows<3>::embed : PaperRows<4>::embed);
+        const Access a = access_kind(n);
+        const RowFn *fn = c == 1 ? PaperEmbed<1>::fn[a] : (c == 3 ? PaperEmbed<3>::fn[a] : PaperEmbed<4>::fn[a]);
         if (launch_rows(fn, p, units, rows, 2, (hipStream_t)stream)) return launched("paper embed kernel launch");
     }
     const uint64_t items = vec ? ceil_div(n, 16) : n;
@@ -148,10 +152,10 @@ int lsb_paper_extract(const uint8_t *stego, uint32_t h, uint32_t w, uint32_t c, 
     p.q = w / 4;
     if (c <= 4) {
         const uint64_t units = ceil_div(p.q < len ? p.q : len, c == 1 ? 16 : 4);
-        const RowFn *fn = c == 1   ? PaperRowsX<1>::extract
-                          : c == 2 ? PaperRowsX<2>::extract
-                          : c == 3 ? PaperRowsX<3>::extract
-                                   : PaperRowsX<4>::extract;
+        const RowFn *fn = c == 1   ? PaperExtract<1>::fn
+                          : c == 2 ? PaperExtract<2>::fn
+                          : c == 3 ? PaperExtract<3>::fn
+                                   : PaperExtract<4>::fn;
         if (launch_rows(fn, p, units, ceil_div(len, p.q), 1, (hipStream_t)stream))
             return launched("paper extract kernel launch");
     }

@@ -353,8 +353,9 @@ __device__ __forceinline__ u32x4 row_general(const PaperSpan &p, const RowVec &t
 // staged the data in LDS and needed aligned rows of 16-byte multiples; other
 // widths, by 16-byte vectors across rows with a gather per byte: 8191x8191x3
 // 159 -> 69 us, 14000x14001x1 174 -> 74 us, 768x1366x3 5.3 -> 4.1 us.
-template <int C, bool SHORT>
+template <int C, bool SHORT, int ACC>
 __global__ void __launch_bounds__(1024) lsb_paper_embed_units_kernel(PaperSpan p, RowMap map, uint64_t n_rows) {
+    constexpr bool NT = ACC != CACHED, NTS = ACC == STREAM;
     constexpr int UNR = 2, ND = RowUnit<C>::ND;
     const uint32_t rowbytes = (uint32_t)p.rowbytes;
     uint64_t pos[UNR];
@@ -380,7 +381,7 @@ __global__ void __launch_bounds__(1024) lsb_paper_embed_units_kernel(PaperSpan p
         uint32_t d[UNR][ND];
 #pragma unroll
         for (int m = 0; m < UNR; ++m) {
-            v[m] = load16<true>(p.src + pos[m]);
+            v[m] = load16<NT>(p.src + pos[m]);
             const u32_any *q = reinterpret_cast<const u32_any *>(at[m]);
 #pragma unroll
             for (int w = 0; w < ND; ++w) d[m][w] = q[w];
@@ -393,16 +394,16 @@ __global__ void __launch_bounds__(1024) lsb_paper_embed_units_kernel(PaperSpan p
                 d[m][w] = (d[m][w] >> shift[m]) & 0x03030303u;
                 kp[w] = 0x03030303u;
             }
-            store16<true>(p.dst + pos[m], place_pairs<C>(p, v[m], d[m], kp, t[m].r));
+            store16<NTS>(p.dst + pos[m], place_pairs<C>(p, v[m], d[m], kp, t[m].r));
         }
         return;
     }
 #pragma unroll
     for (int m = 0; m < UNR; ++m)
-        if (any[m]) v[m] = load16<true>(p.src + pos[m]);
+        if (any[m]) v[m] = load16<NT>(p.src + pos[m]);
 #pragma unroll
     for (int m = 0; m < UNR; ++m)
-        if (any[m]) store16<true>(p.dst + pos[m], row_general<C>(p, t[m], v[m]));
+        if (any[m]) store16<NTS>(p.dst + pos[m], row_general<C>(p, t[m], v[m]));
 }
 
 // Four plane bytes of the four pixels whose C * 4 bytes are in d (Section VII

@@ -95,40 +95,48 @@ __global__ void __launch_bounds__(kSseBlock) lsb_sse_kernel(const uint8_t *a, co
 typedef void (*PlaneEmbedFn)(Span, uint32_t, uint64_t, uint64_t);
 typedef void (*PlaneExtractFn)(Span, uint32_t, uint64_t, uint32_t *, int32_t *);
 
+// [access kind or streaming loads][channels - 2]
 template <int K>
 struct PlaneTable {
-    static constexpr PlaneEmbedFn embed[3] = {lsb_plane_embed_vec_kernel<K, 2>, lsb_plane_embed_vec_kernel<K, 3>,
-                                              lsb_plane_embed_vec_kernel<K, 4>};
-    static constexpr PlaneExtractFn extract[3] = {lsb_plane_extract_vec_kernel<K, 2>,
-                                                  lsb_plane_extract_vec_kernel<K, 3>,
-                                                  lsb_plane_extract_vec_kernel<K, 4>};
+    static constexpr PlaneEmbedFn embed[3][3] = {
+        {lsb_plane_embed_vec_kernel<K, 2, CACHED>, lsb_plane_embed_vec_kernel<K, 3, CACHED>,
+         lsb_plane_embed_vec_kernel<K, 4, CACHED>},
+        {lsb_plane_embed_vec_kernel<K, 2, STREAM_LOADS>, lsb_plane_embed_vec_kernel<K, 3, STREAM_LOADS>,
+         lsb_plane_embed_vec_kernel<K, 4, STREAM_LOADS>},
+        {lsb_plane_embed_vec_kernel<K, 2, STREAM>, lsb_plane_embed_vec_kernel<K, 3, STREAM>,
+         lsb_plane_embed_vec_kernel<K, 4, STREAM>}};
+    static constexpr PlaneExtractFn extract[2][3] = {
+        {lsb_plane_extract_vec_kernel<K, 2, false>, lsb_plane_extract_vec_kernel<K, 3, false>,
+         lsb_plane_extract_vec_kernel<K, 4, false>},
+        {lsb_plane_extract_vec_kernel<K, 2, true>, lsb_plane_extract_vec_kernel<K, 3, true>,
+         lsb_plane_extract_vec_kernel<K, 4, true>}};
 };
 
-static PlaneEmbedFn plane_embed_fn(int k, uint32_t c) {
+static PlaneEmbedFn plane_embed_fn(int k, uint32_t c, Access a) {
     const int ci = (int)c - 2;
     switch (k) {
-        case 1: return PlaneTable<1>::embed[ci];
-        case 2: return PlaneTable<2>::embed[ci];
-        case 3: return PlaneTable<3>::embed[ci];
-        case 4: return PlaneTable<4>::embed[ci];
-        case 5: return PlaneTable<5>::embed[ci];
-        case 6: return PlaneTable<6>::embed[ci];
-        case 7: return PlaneTable<7>::embed[ci];
-        default: return PlaneTable<8>::embed[ci];
+        case 1: return PlaneTable<1>::embed[a][ci];
+        case 2: return PlaneTable<2>::embed[a][ci];
+        case 3: return PlaneTable<3>::embed[a][ci];
+        case 4: return PlaneTable<4>::embed[a][ci];
+        case 5: return PlaneTable<5>::embed[a][ci];
+        case 6: return PlaneTable<6>::embed[a][ci];
+        case 7: return PlaneTable<7>::embed[a][ci];
+        default: return PlaneTable<8>::embed[a][ci];
     }
 }
 
-static PlaneExtractFn plane_extract_fn(int k, uint32_t c) {
+static PlaneExtractFn plane_extract_fn(int k, uint32_t c, bool nt) {
     const int ci = (int)c - 2;
     switch (k) {
-        case 1: return PlaneTable<1>::extract[ci];
-        case 2: return PlaneTable<2>::extract[ci];
-        case 3: return PlaneTable<3>::extract[ci];
-        case 4: return PlaneTable<4>::extract[ci];
-        case 5: return PlaneTable<5>::extract[ci];
-        case 6: return PlaneTable<6>::extract[ci];
-        case 7: return PlaneTable<7>::extract[ci];
-        default: return PlaneTable<8>::extract[ci];
+        case 1: return PlaneTable<1>::extract[nt][ci];
+        case 2: return PlaneTable<2>::extract[nt][ci];
+        case 3: return PlaneTable<3>::extract[nt][ci];
+        case 4: return PlaneTable<4>::extract[nt][ci];
+        case 5: return PlaneTable<5>::extract[nt][ci];
+        case 6: return PlaneTable<6>::extract[nt][ci];
+        case 7: return PlaneTable<7>::extract[nt][ci];
+        default: return PlaneTable<8>::extract[nt][ci];
     }
 }
 
@@ -183,8 +191,8 @@ int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels, uint3
         const uint64_t blocks = std::min<uint64_t>(ceil_div(count, 512), 0xFFFFFFFFull / 256);
         hipEvent_t e0, e1;
         take_launch_events(&e0, &e1);
-        hipExtLaunchKernelGGL(plane_embed_fn(k, c), dim3((unsigned)blocks), dim3(256), 0, st, e0, e1, 0, s, plane, n,
-                              count);
+        hipExtLaunchKernelGGL(plane_embed_fn(k, c, access_kind(n)), dim3((unsigned)blocks), dim3(256), 0, st, e0, e1,
+                              0, s, plane, n, count);
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? LSB_OK : hip_fail(e, "plane embed kernel launch");
     }
@@ -243,8 +251,8 @@ int lsb_extract_plane(const uint8_t *stego, uint64_t pixels, uint32_t c, uint32_
             const uint64_t v_buf = ceil_div(pixels, 16);
             vectors = v_stream < v_buf ? v_stream : v_buf;
         }
-        hipExtLaunchKernelGGL(plane_extract_fn(k, c), dim3(grid_cap(vectors)), dim3(256), 0, (hipStream_t)stream, e0,
-                              e1, 0, s, plane, out_cap, len_out_dev, status_out_dev);
+        hipExtLaunchKernelGGL(plane_extract_fn(k, c, access_kind(n) != CACHED), dim3(grid_cap(vectors)), dim3(256), 0,
+                              (hipStream_t)stream, e0, e1, 0, s, plane, out_cap, len_out_dev, status_out_dev);
     } else {
         hipExtLaunchKernelGGL(lsb_plane_extract_kernel, dim3(grid_cap(max_len)), dim3(256), 0, (hipStream_t)stream,
                               e0, e1, 0, s, c, plane, out_cap, len_out_dev, status_out_dev);

@@ -128,10 +128,10 @@ __device__ __forceinline__ u32x4 plane_gather_any(const u32x4 *v, uint32_t plane
 // 16*C bytes.  Other groups (header, stream end, buffer tail) go lane by lane.
 
 // stage[64*i + lane] = vector 64*i + lane of the group.
-template <int C>
+template <int C, bool NT>
 __device__ __forceinline__ void plane_group_load(const uint8_t *src, u32x4 *stage, uint32_t lane) {
 #pragma unroll
-    for (int i = 0; i < C; ++i) stage[64 * i + lane] = load16<true>(src + 16 * (64 * i + lane));
+    for (int i = 0; i < C; ++i) stage[64 * i + lane] = load16<NT>(src + 16 * (64 * i + lane));
 }
 
 // Embed of a plane, 16-byte vectors of the interleaved buffer.  A vector holds
@@ -205,9 +205,10 @@ __device__ __forceinline__ uint64_t plane_bits_edge(const Span &s, uint64_t x, u
 // plain embed.  Against 16 pixels per lane exchanged through LDS (the first
 // and last of them byte by byte): 512x512x3 11.1 -> 4.2 us, 3000x4000x3 18.8
 // -> 13.7 us, 8192x8192x3 74.2 -> 64.1 us (6.5 TB/s).
-template <int K, int C>
+template <int K, int C, int ACC>
 __global__ void __launch_bounds__(256)
     lsb_plane_embed_vec_kernel(Span s, uint32_t plane, uint64_t bytes, uint64_t count) {
+    constexpr bool NT = ACC != CACHED, NTS = ACC == STREAM;
     constexpr int UNR = 2, W = PlaneVec<C>::W;
     const uint8_t *body = s.body - s.hdr_len;  // stream byte i at body + i
     const uint64_t end = s.bits / 8;           // whole stream bytes (header mode: bits is a multiple of 8)
@@ -236,7 +237,7 @@ __global__ void __launch_bounds__(256)
             uint64_t w[UNR];
 #pragma unroll
             for (int m = 0; m < UNR; ++m) {
-                v[m] = load16<true>(s.src + at[m]);
+                v[m] = load16<NT>(s.src + at[m]);
                 const u32_any *p = reinterpret_cast<const u32_any *>(body + (((uint64_t)K * x[m]) >> 3));
                 w[m] = (uint64_t)bswap32(p[0]) << 32 | bswap32(p[1]);
             }
@@ -245,7 +246,7 @@ __global__ void __launch_bounds__(256)
                 const uint32_t sh = (uint32_t)((uint64_t)K * x[m]) & 7u;
                 const u32x4 f = spread_fields<C>(unpack_fields<K, W>(w[m] << sh), r[m]);
                 const u32x4 keep = spread_fields<C>(((1u << K) - 1u) * 0x0101010101010101ull, r[m]);
-                store16<true>(s.dst + at[m], (v[m] & ~keep) | f);
+                store16<NTS>(s.dst + at[m], (v[m] & ~keep) | f);
             }
         } else {
 #pragma unroll 1
@@ -255,7 +256,7 @@ __global__ void __launch_bounds__(256)
                 const uint64_t w = plane_bits_edge<K, W>(s, x[m], &nb);
                 if (nb == 0 && s.inplace) continue;
                 const uint32_t nbytes = bytes - at[m] < 16 ? (uint32_t)(bytes - at[m]) : 16;
-                const u32x4 v = load_bytes<true>(s.src + at[m], nbytes);
+                const u32x4 v = load_bytes<NT>(s.src + at[m], nbytes);
                 const u32x4 f = spread_fields<C>(unpack_fields<K, W>(w), r[m]);
                 const u32x4 keep = spread_fields<C>(
                     unpack_fields<K, W>(nb >= 64 ? ~0ull : ~(~0ull >> nb)), r[m]);
@@ -263,7 +264,7 @@ __global__ void __launch_bounds__(256)
                 // in place nothing past the last stream-carrying byte is written
                 const uint32_t carry = r[m] + C * ((nb + K - 1) / K) - (C - 1);
                 const uint32_t hi = s.inplace && carry < nbytes ? carry : nbytes;
-                if (hi == 16) store16<true>(s.dst + at[m], o);
+                if (hi == 16) store16<NTS>(s.dst + at[m], o);
                 else store_bytes<16>(s.dst + at[m], o, 0, hi);
             }
         }
@@ -306,7 +307,7 @@ __device__ __forceinline__ void plane_extract_unit(const Span &s, const Ranges &
 
 // Extract over the plane view: header decode per wave (lane j < 32 reads
 // stream bit j), status through block 0, then 2K message bytes per lane.
-template <int K, int C>
+template <int K, int C, bool NT>
 __global__ void __launch_bounds__(256)
     lsb_plane_extract_vec_kernel(Span s, uint32_t plane, uint64_t out_cap, uint32_t *len_out, int32_t *status_out) {
     __shared__ u32x4 stage_all[4][64 * C];
@@ -335,7 +336,7 @@ __global__ void __launch_bounds__(256)
     for (uint64_t g = wave; g < groups; g += n_waves) {
         const uint64_t u0 = 64 * g;
         if (u0 >= r.fast_begin && u0 + 64 <= r.fast_end) {
-            plane_group_load<C>(s.src + 16 * C * u0, stage, lane);
+            plane_group_load<C, NT>(s.src + 16 * C * u0, stage, lane);
             __builtin_amdgcn_wave_barrier();
             plane_group_extract<K, C>(s, stage, u0 + lane, lane, plane);
             __builtin_amdgcn_wave_barrier();

@@ -165,3 +165,26 @@ def test_plane_vectors(k, c):
                 got = to_host(big)
                 assert_bytes_equal(got[16:16 + cover.size], want, tag)
                 assert (got[:16] == 0x77).all() and (got[16 + cover.size:] == 0x77).all(), tag
+
+
+@pytest.mark.parametrize("h,w", [(3000, 4444), (3000, 4445), (5461, 8192), (5462, 8192)])
+def test_access_kinds_by_size(h, w):
+    """Images just below and above 40 MB and 2^27 bytes (cached accesses,
+    streaming loads, streaming stores): plane embed and extract, and the
+    paper's layout, against the oracle."""
+    c, plane, k = 3, 1, 2
+    n = h * w * c
+    cover = inputs.random_bytes(n, 2831)
+    msg = inputs.random_bytes(oracle.capacity(h * w, k) - 9, 2832)
+    rc, want = oracle.embed_plane(cover, c, plane, msg, k)
+    cover_d = to_dev(cover)
+    stego = api.embed_plane(cover_d, c, plane, to_dev(msg), k)
+    assert_bytes_equal(to_host(stego), want, "plane embed")
+    out, ls = api.extract_plane(stego, c, plane, k)
+    assert ls.cpu().tolist() == [msg.size, OK]
+    assert_bytes_equal(to_host(out)[:msg.size], msg, "plane extract")
+    data = msg[:oracle.paper_capacity(h, w) - 5]
+    rc, want = oracle.paper_embed(cover, h, w, c, plane, data)
+    stego = api.paper_embed(cover_d, h, w, c, plane, to_dev(data))
+    assert_bytes_equal(to_host(stego), want, "paper embed")
+    assert_bytes_equal(to_host(api.paper_extract(stego, h, w, c, plane, data.size)), data, "paper extract")
