@@ -666,3 +666,34 @@ def test_job_index_levels(count, restore_tiles):
         assert_bytes_equal(got, want, "%d jobs" % count)
     finally:
         plan.close()
+
+
+def test_later_runs_and_updates_wait_for_a_run():
+    """A plan's completion event is bound to its kernel: a run on another
+    stream starts after the plan's previous run, and an update returns only
+    when the runs before it are over.  (Several milliseconds of runs are in
+    flight each time; the other stream is idle.)"""
+    wl = BatchWorkload(64, oracle.capacity, seed=446, lo=3000, hi=4096)
+    cover, stego, msg, _ = wl.allocate(DEV)
+    status = torch.full((wl.count,), 99, dtype=torch.int32, device=DEV)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()  # default priority
+    plan = batch.Plan(wl.count, OP_EMBED, wl.jobs(OP_EMBED))
+    torch.cuda.synchronize()
+    try:
+        for _ in range(2):
+            for _ in range(30):
+                plan.embed_batch(cover, stego, msg, status, stream=a)
+            busy = not a.query()
+            plan.embed_batch(cover, stego, msg, status, stream=b)
+            b.synchronize()
+            assert busy and a.query(), "the run on b overtook the runs on a"
+        for _ in range(30):
+            plan.embed_batch(cover, stego, msg, status, stream=a)
+        busy = not a.query()
+        plan.set_jobs(wl.jobs(OP_EMBED)[::-1].copy())
+        assert busy and a.query(), "the update did not wait for the runs"
+        plan.embed_batch(cover, stego, msg, status, stream=b)
+        torch.cuda.synchronize()
+    finally:
+        plan.close()
+    assert bool((status == OK).all())
