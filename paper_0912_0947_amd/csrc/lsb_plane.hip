@@ -46,6 +46,7 @@ __device__ __forceinline__ uint32_t sq_diff16(u32x4 x, u32x4 y, uint32_t acc) {
 // x 36 MB 22.6 -> 14.1 us, 2 x 201 MB 65.0 -> 60.3 us (6.7 TB/s); 256 blocks
 // of 1024 threads 5.8 / 15.7 / 61.4 us, 512 blocks of 512 5.7 / 16.3 / 61.6 us.
 constexpr int kSseUnroll = 4, kSseBlocksPerCu = 1, kSseBlock = 512;
+template <bool NT>
 __global__ void __launch_bounds__(kSseBlock) lsb_sse_kernel(const uint8_t *a, const uint8_t *b, uint64_t n,
                                                      unsigned long long *out) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -58,14 +59,14 @@ __global__ void __launch_bounds__(kSseBlock) lsb_sse_kernel(const uint8_t *a, co
             u32x4 x[kSseUnroll], y[kSseUnroll];
 #pragma unroll
             for (int j = 0; j < kSseUnroll; ++j) {
-                x[j] = load16<true>(a + 16 * (u0 + kSseBlock * j));
-                y[j] = load16<true>(b + 16 * (u0 + kSseBlock * j));
+                x[j] = load16<NT>(a + 16 * (u0 + kSseBlock * j));
+                y[j] = load16<NT>(b + 16 * (u0 + kSseBlock * j));
             }
 #pragma unroll
             for (int j = 0; j < kSseUnroll; ++j) sum = sq_diff16(x[j], y[j], sum);
         } else {
             for (uint64_t u = u0; u < nv && u < u0 + kSseBlock * kSseUnroll; u += kSseBlock)
-                sum = sq_diff16(load16<true>(a + 16 * u), load16<true>(b + 16 * u), sum);
+                sum = sq_diff16(load16<NT>(a + 16 * u), load16<NT>(b + 16 * u), sum);
         }
         acc += sum;
     }
@@ -274,7 +275,10 @@ int lsb_sse(const uint8_t *a, const uint8_t *b, uint64_t n, uint64_t *sse_dev, v
     uint64_t blocks = ceil_div(n / 16 + 1, kSseBlock * kSseUnroll);
     const uint64_t cap = (uint64_t)device_cus() * kSseBlocksPerCu;
     if (blocks > cap) blocks = cap;
-    hipExtLaunchKernelGGL(lsb_sse_kernel, dim3((unsigned)blocks), dim3(kSseBlock), 0, st, e0, e1, 0, a, b, n,
+    // cached loads while the buffers may still be in the caches (they stream
+    // at 64 MB: a check pass 68.2 us streaming, 69.3 cached; 36 MB 44.4, 42.9)
+    const auto fn = access_kind(n) == CACHED ? lsb_sse_kernel<false> : lsb_sse_kernel<true>;
+    hipExtLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kSseBlock), 0, st, e0, e1, 0, a, b, n,
                           (unsigned long long *)sse_dev);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? LSB_OK : hip_fail(e, "sse kernel launch");

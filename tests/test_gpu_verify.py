@@ -126,3 +126,23 @@ def test_verify_counts_each_kind_of_corruption(k):
         assert want > 0
         got = int(api.verify(c_d, to_dev(bad), m_d, k).item())
         assert got == want, "k=%d %s: counted %d of %d wrong bytes" % (k, name, got, want)
+
+
+@pytest.mark.parametrize("n", [39_999_999, 40_000_001, (1 << 27) - 3, (1 << 27) + 5])
+def test_access_kinds_by_size(n):
+    """Covers around 40 MB and 2^27 bytes (cached and streaming accesses):
+    checked embed, check of a stego with wrong bytes, squared error."""
+    k = 2
+    cover = torch.empty(n, dtype=torch.uint8, device=DEV)
+    inputs.fill_uniform(cover, 2911)
+    msg = torch.empty(oracle.capacity(n, k) - 3, dtype=torch.uint8, device=DEV)
+    inputs.fill_uniform(msg, 2912)
+    stego, wrong = api.embed_verify(cover, msg, k)
+    assert int(wrong) == 0 and int(api.verify(cover, stego, msg, k)) == 0
+    assert torch.equal(stego, api.embed(cover, msg, k))
+    at = torch.arange(7, n, n // 41, device=DEV)
+    stego[at] ^= 1
+    assert int(api.verify(cover, stego, msg, k)) == at.numel()
+    want = sum(int(((a.to(torch.int32) - b.to(torch.int32)) ** 2).sum(dtype=torch.int64))
+               for a, b in zip(cover.split(1 << 24), stego.split(1 << 24)))
+    assert int(api.sse(cover, stego)) == want
