@@ -15,7 +15,6 @@
 // host mirror, only when the table changed since the last upload, then the
 // kernel, which also reports each job's status (and, for extract jobs, the
 // decoded length).  Nothing on the device changes between runs but outputs.
-#include <hip/hip_ext.h>
 #include <stddef.h>
 #include <string.h>
 
@@ -240,14 +239,10 @@ static unsigned main_grid_for(const lsb_launch_cfg &cfg, uint64_t total_tiles) {
     return (unsigned)std::min(cap, std::max<uint64_t>(total_tiles, 1));
 }
 
-// Launch the kernel of a filled, uploaded table.  `done` (may be null) is
-// recorded by the kernel's own completion: recorded behind it, it was a packet
-// of its own that the next run waited for (3 us a run: 75 covers of 64..121 px,
-// embed + extract, 16.8 us against 10.0).
+// Launch the kernel of a filled, uploaded table.
 static hipError_t launch_batch(const lsb_launch_cfg &cfg, const TableInfo &t, int n_jobs, int64_t tv,
                                const uint8_t *table, const uint8_t *cover_arena, uint8_t *stego_arena,
-                               uint8_t *msg_arena, uint32_t *len_dev, int32_t *status_dev, hipStream_t st,
-                               hipEvent_t done) {
+                               uint8_t *msg_arena, uint32_t *len_dev, int32_t *status_dev, hipStream_t st) {
     const TableLayout lay = table_layout((uint64_t)n_jobs);
     BatchArgs a{};
     a.jobs = (const DevJob *)table;
@@ -264,8 +259,8 @@ static hipError_t launch_batch(const lsb_launch_cfg &cfg, const TableInfo &t, in
     a.status_dev = status_dev;
     a.empty_jobs = t.has_empty;
     void *argv[] = {&a};
-    return hipExtLaunchKernel((const void *)batch_fn(cfg.unroll, cfg.nontemporal, t.cls, t.has_raw),
-                              dim3(main_grid_for(cfg, t.tiles)), dim3(cfg.block), argv, 0, st, nullptr, done, 0);
+    return hipLaunchKernel((const void *)batch_fn(cfg.unroll, cfg.nontemporal, t.cls, t.has_raw),
+                           dim3(main_grid_for(cfg, t.tiles)), dim3(cfg.block), argv, 0, st);
 }
 
 static int64_t batch_tile_vectors() {
@@ -294,7 +289,14 @@ int lsb_plan_create(lsb_plan **out, const lsb_job *jobs, int n_jobs, int op) {
     e = hipMalloc((void **)&p->dev, p->table_bytes);
     if (e != hipSuccess)
         return (void)hipHostFree(p->host), delete p, fail(LSB_E_NOMEM, "lsb_plan_create: hipMalloc failed");
-    e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming);
+    // Nothing the host or another device reads hangs on this event (it orders
+    // later uploads and runs on this device, and the freeing of the table), so
+    // it needs no system-wide fence, which the next run on the stream would
+    // wait for: 4096 covers of 64..256 px, embed + extract, 117.3 -> 114.0 us;
+    // 25 frames of 720p 40.8 -> 37.4 us.  (Bound to the kernel as its stop event
+    // it is cheaper still, 111.6 and 35.1 us, but after thousands of runs in
+    // flight the runtime then takes milliseconds to clear the launches.)
+    e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) return (void)hipFree(p->dev), (void)hipHostFree(p->host), delete p, hip_fail(e, "hipEventCreate");
     memset(p->host, 0, p->table_bytes);
     if (jobs) {
@@ -413,13 +415,19 @@ int lsb_plan_run(lsb_plan *p, const uint8_t *cover_arena, uint8_t *stego_arena, 
         e = hipMemcpyAsync(p->dev, p->host, p->info.used_bytes, hipMemcpyHostToDevice, st);
         if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(job table)");
     }
-    e = launch_batch(cfg, p->info, p->n_jobs, tv, p->dev, cover_arena, stego_arena, msg_arena, len_dev, status_dev, st,
-                     p->done);
+    e = launch_batch(cfg, p->info, p->n_jobs, tv, p->dev, cover_arena, stego_arena, msg_arena, len_dev, status_dev, st);
     if (e != hipSuccess) {
         // an enqueued upload still reads the pinned mirror: let it finish
         // before a later update may refill the mirror
         if (upload) (void)hipStreamSynchronize(st);
         return hip_fail(e, "batched kernel launch");
+    }
+    e = hipEventRecord(p->done, st);
+    if (e != hipSuccess) {
+        // without the event nothing tracks the launch: wait for it here so
+        // that a later update or destroy cannot overtake it
+        (void)hipStreamSynchronize(st);
+        return hip_fail(e, "hipEventRecord(plan)");
     }
     p->ran = true;
     p->table_dirty = false;
@@ -500,7 +508,7 @@ int lsb_batch_run_static(const lsb_job *jobs, int n_jobs, int op, const uint8_t 
     if (t.has_embed && !cover_arena) return fail(LSB_E_ARG, "lsb_batch_run_static: embed jobs need a cover arena");
     e = hipMemcpyAsync(table, g_static_host, t.used_bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(static job table)");
-    e = launch_batch(cfg, t, n_jobs, tv, table, cover_arena, stego_arena, msg_arena, len_dev, status_dev, st, nullptr);
+    e = launch_batch(cfg, t, n_jobs, tv, table, cover_arena, stego_arena, msg_arena, len_dev, status_dev, st);
     if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
     return LSB_OK;
 }

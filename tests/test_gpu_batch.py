@@ -669,9 +669,9 @@ def test_job_index_levels(count, restore_tiles):
 
 
 def test_later_runs_and_updates_wait_for_a_run():
-    """A plan's completion event is bound to its kernel: a run on another
-    stream starts after the plan's previous run, and an update returns only
-    when the runs before it are over.  (Several milliseconds of runs are in
+    """A plan's completion event carries no system-wide fence, but it still
+    orders: a run on another stream starts after the plan's previous run, and
+    an update returns only when the runs before it are over.  (Several milliseconds of runs are in
     flight each time; the other stream is idle.)"""
     wl = BatchWorkload(64, oracle.capacity, seed=446, lo=3000, hi=4096)
     cover, stego, msg, _ = wl.allocate(DEV)
