@@ -330,7 +330,7 @@ int lsb_job_extents(const lsb_job *jobs, int n_jobs, int op,
 /* For callers that cannot allocate (serving loops and harnesses that may not
  * call hipMalloc): lsb_plan_create + lsb_plan_run in one call that allocates
  * nothing.  The job table goes into a
- * fixed device array of the library (one per device, about 256 KiB, held
+ * fixed device array of the library (one per device, about 370 KiB, held
  * until the process ends) instead of plan memory; the table is staged in a
  * library host buffer and uploaded with an asynchronous copy on `stream`,
  * then the batched kernel is launched on `stream` (no graph).  Jobs, arenas, len_dev and status_dev mean what they mean for
