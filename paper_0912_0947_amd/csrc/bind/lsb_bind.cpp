@@ -12,11 +12,18 @@
 //
 // The library's functions are looked up in the handle that the Python layer
 // has loaded (install); the GIL is released around each call, as ctypes does.
+//
+// Reading a tensor can throw (storage that refuses to hand out its address, a
+// lazy copy that finds no memory): no C++ exception may reach CPython, so each
+// function declines then, and the checked path meets the same refusal as a
+// Python error.
 #include <Python.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <exception>
 
 #include "../../../include/lsb.h"
 
@@ -124,6 +131,17 @@ PyObject *call(const Args &a, F f) {
     int64_t rc;
     Py_BEGIN_ALLOW_THREADS rc = f();
     Py_END_ALLOW_THREADS return PyLong_FromLongLong(rc);
+}
+
+typedef PyObject *(*BindFn)(PyObject *, PyObject *const *, Py_ssize_t);
+
+template <BindFn f>
+PyObject *guarded(PyObject *self, PyObject *const *args, Py_ssize_t given) {
+    try {
+        return f(self, args, given);
+    } catch (const std::exception &) {
+        Py_RETURN_NONE;
+    }
 }
 
 #define LSB_BIND(name) PyObject *name(PyObject *, PyObject *const *args, Py_ssize_t given)
@@ -334,7 +352,7 @@ PyObject *install(PyObject *, PyObject *arg) {
     return nullptr;
 }
 
-#define LSB_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
+#define LSB_METHOD(name) {#name, (PyCFunction)(void (*)(void))guarded<name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {LSB_METHOD(capacity), LSB_METHOD(embed), LSB_METHOD(extract), LSB_METHOD(extract_sync),
                          LSB_METHOD(embed_raw), LSB_METHOD(extract_raw), LSB_METHOD(paper_embed),
                          LSB_METHOD(paper_extract), LSB_METHOD(embed_plane), LSB_METHOD(extract_plane),

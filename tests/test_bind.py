@@ -102,3 +102,38 @@ def test_same_as_the_checked_path(monkeypatch):
     with pytest.raises(Exception):
         torch.vmap(lambda x: seen.append(_lib.bind().embed(x, x, msg, k, None)) or api.embed(x, msg, k))(cover.view(3, -1))
     assert seen == [None]
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(not hasattr(torch._C, "_set_throw_on_mutable_data_ptr"), reason="needs torch's data-pointer trap")
+@pytest.mark.parametrize("name", ["embed", "extract", "extract_sync", "embed_raw", "extract_raw", "sse", "verify",
+                                  "embed_verify", "embed_plane", "extract_plane", "paper_embed", "paper_extract"])
+def test_a_refusing_tensor_is_an_error(name):
+    """A tensor whose storage throws when its address is read: the module
+    declines (a C++ exception that reached the interpreter would end the
+    process) and the call raises torch's error."""
+    from gpu_helpers import DEV
+
+    n = 4096
+    bad, good = (torch.zeros(n, dtype=torch.uint8, device=DEV) for _ in range(2))
+    msg = torch.zeros(16, dtype=torch.uint8, device=DEV)
+    ls, word = torch.zeros(2, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+    torch._C._set_throw_on_mutable_data_ptr(bad)
+    args = {"embed": (bad, good, msg, 1, None), "extract": (bad, good, ls, 1, None),
+            "extract_sync": (bad, good, 1, None), "embed_raw": (bad, good, 0, msg, 128, 1, None),
+            "extract_raw": (bad, 0, good, 128, 1, None), "sse": (bad, good, word, None),
+            "verify": (bad, good, msg, 1, word, None), "embed_verify": (bad, good, msg, 1, word, None),
+            "embed_plane": (bad, good, 4, 0, msg, 1, None), "extract_plane": (bad, good, ls, 4, 0, 1, None),
+            "paper_embed": (bad, good, 32, 32, 4, 0, msg, None),
+            "paper_extract": (bad, good, 32, 32, 4, 0, 16, None)}[name]
+    assert getattr(_lib.bind(), name)(*args) is None
+    calls = {"embed": lambda: api.embed(bad, msg, 1), "extract": lambda: api.extract(bad, 1),
+             "extract_sync": lambda: api.extract_sync(bad, 1), "embed_raw": lambda: api.embed_raw(bad, 0, msg, 128, 1),
+             "extract_raw": lambda: api.extract_raw(bad, 0, good, 128, 1), "sse": lambda: api.sse(bad, good),
+             "verify": lambda: api.verify(bad, good, msg, 1), "embed_verify": lambda: api.embed_verify(bad, msg, 1),
+             "embed_plane": lambda: api.embed_plane(bad, 4, 0, msg, 1),
+             "extract_plane": lambda: api.extract_plane(bad, 4, 0, 1),
+             "paper_embed": lambda: api.paper_embed(bad, 32, 32, 4, 0, msg),
+             "paper_extract": lambda: api.paper_extract(bad, 32, 32, 4, 0, 16)}
+    with pytest.raises(RuntimeError, match="data pointer"):
+        calls[name]()
