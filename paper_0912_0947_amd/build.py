@@ -63,6 +63,29 @@ def bind_command(out: str) -> list[str]:
             "-Wl,-rpath," + libs]
 
 
+def start_bind(out: str) -> subprocess.Popen | None:
+    """Start the marshalling module's build; None if this torch cannot say how."""
+    try:
+        return subprocess.Popen(bind_command(out), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    except (ImportError, OSError, RuntimeError) as e:
+        print("the marshalling module cannot be built: %s" % e, file=sys.stderr, flush=True)
+        return None
+
+
+def finish_bind(proc: subprocess.Popen | None, out: str) -> bool:
+    """Put the built marshalling module in place.  Without it every call still
+    works, through the checked path, so its failure does not fail the build;
+    a module of an earlier build must not stay beside the new library."""
+    text = proc.communicate()[0] if proc else ""
+    if proc and proc.returncode == 0:
+        os.replace(out, BIND)
+        return True
+    print("the marshalling module was not built; calls will take the checked path\n" + text, file=sys.stderr, flush=True)
+    if os.path.exists(BIND):
+        os.remove(BIND)
+    return False
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every source to an object (in parallel), then link liblsb.so;
     the marshalling module builds beside them."""
@@ -71,8 +94,8 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(objdir, exist_ok=True)
     t0 = time.time()
     bind_tmp = BIND + ".tmp%d" % os.getpid()
-    procs = [(BIND_SOURCE, subprocess.Popen(bind_command(bind_tmp), stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
-                                            text=True))]
+    bind = start_bind(bind_tmp)
+    procs = []
     objs = []
     for src in sources():
         obj = os.path.join(objdir, os.path.basename(src) + ".o")
@@ -96,7 +119,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp, *objs, *LINK_FLAGS])
     os.replace(tmp, LIB)
-    os.replace(bind_tmp, BIND)
+    finish_bind(bind, bind_tmp)
     if verbose:
         print("built %s in %.1f s" % (LIB, time.time() - t0), flush=True)
     return LIB

@@ -137,3 +137,44 @@ def test_a_refusing_tensor_is_an_error(name):
              "paper_extract": lambda: api.paper_extract(bad, 32, 32, 4, 0, 16)}
     with pytest.raises(RuntimeError, match="data pointer"):
         calls[name]()
+
+
+def test_without_the_module(monkeypatch):
+    """liblsb.so alone is enough: where the module does not load, every call
+    is declined and takes the checked path."""
+    import sys
+
+    import paper_0912_0947_amd as package
+
+    handle = _lib.lib()
+    monkeypatch.setattr(_lib, "_bind", _lib._bind)
+    monkeypatch.setitem(sys.modules, package.__name__ + "._bind", None)  # its import fails
+    monkeypatch.delattr(package, "_bind", raising=False)
+    with pytest.warns(RuntimeWarning, match="checked path"):
+        _lib._install(handle)
+    assert _lib.bind().embed(1, 2, 3) is None and _lib.bind().capacity(100, 1) is None
+    assert api.capacity(786432, 1) == 98300
+    t = torch.zeros(64, dtype=torch.uint8)
+    with pytest.raises(TypeError, match="GPU"):
+        api.embed(t, t, 1)
+
+
+@pytest.mark.parametrize("starts", [True, False])
+def test_build_without_the_module(monkeypatch, tmp_path, capsys, starts):
+    """A marshalling module that does not build leaves the library's build
+    standing, and no module of an earlier build."""
+    from paper_0912_0947_amd import build
+
+    stale = tmp_path / "_bind.so"
+    stale.write_bytes(b"earlier")
+    monkeypatch.setattr(build, "BIND", str(stale))
+
+    def command(out):
+        if not starts:
+            raise ImportError("no torch headers")
+        return ["false"]
+
+    monkeypatch.setattr(build, "bind_command", command)
+    out = str(tmp_path / "out.so")
+    assert build.finish_bind(build.start_bind(out), out) is False
+    assert not stale.exists() and "checked path" in capsys.readouterr().err
