@@ -40,9 +40,9 @@
  *   - Threads: every call may be made from several host threads at once,
  *     except that one lsb_plan is used by one thread at a time (distinct
  *     plans are independent).  The shared state is the launch-configuration
- *     tables (guarded; a launch uses the entry current at its call) and
- *     per-thread state (error message, lsb_time_next_launch events,
- *     lsb_extract_sync buffer).
+ *     tables (guarded; a launch uses the entry current at its call), the
+ *     result words of waited extracts (guarded) and per-thread state (error
+ *     message, lsb_time_next_launch events).
  *   - Devices: calls launch on the current HIP device; a plan belongs to the
  *     device current when it was created.
  */
@@ -92,8 +92,10 @@ int lsb_extract(const uint8_t *stego, uint64_t n, int k, uint8_t *msg_out,
 
 /* As lsb_extract, then waits for the stream and returns the device status
  * as the return value (LSB_OK, LSB_E_HEADER, LSB_E_BUFFER) with the decoded
- * length in *len_out_host.  Uses a few words of pinned host memory per
- * thread and device that are allocated on the first call. */
+ * length in *len_out_host.  Uses a line of pinned host memory that the
+ * call takes from a list of the device and gives back: 4 KiB are allocated
+ * when the list is empty (the first call; more than 32 calls waiting at once)
+ * and held until the process ends. */
 int lsb_extract_sync(const uint8_t *stego, uint64_t n, int k,
                      uint8_t *msg_out, uint64_t out_cap,
                      uint32_t *len_out_host, void *stream);

@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "lsb_host.hpp"
+#include "lsb_wait_lines.hpp"
 
 namespace lsb {
 
@@ -191,6 +192,10 @@ int launch_extract(const Span &s0, int header, uint64_t out_cap, uint32_t *len_o
     return e == hipSuccess ? LSB_OK : hip_fail(e, "extract kernel launch");
 }
 
+// Result words of waited extracts, per device.
+constexpr int kWaitDevices = 16;
+static WaitLines g_wait[kWaitDevices];
+
 }  // namespace lsb
 
 using namespace lsb;
@@ -345,29 +350,30 @@ int lsb_extract_raw(const uint8_t *stego, uint64_t n, uint64_t t0, uint8_t *stre
 
 int lsb_extract_sync(const uint8_t *stego, uint64_t n, int k, uint8_t *msg_out, uint64_t out_cap,
                      uint32_t *len_out_host, void *stream) {
-    // Length and status words in pinned host memory, per thread and device:
-    // the kernel writes them there itself, so that the only thing after it is
-    // the wait.  (Through device words and a copy to the stack the waited
-    // embed + extract pass of a 4 KiB cover took 28.7 us, now 18.8 us.)
-    static thread_local uint32_t *scratch[16] = {};
+    // Length and status words in pinned host memory: the kernel writes them
+    // there itself, so that the only thing after it is the wait.  (Through
+    // device words and a copy to the stack the waited embed + extract pass of a
+    // 4 KiB cover took 28.7 us, now 18.8 us.)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-    if (dev < 0 || dev >= 16) return fail(LSB_E_ARG, "lsb_extract_sync: device %d not supported", dev);
-    if (!scratch[dev]) {
-        e = hipHostMalloc((void **)&scratch[dev], 256, hipHostMallocDefault);
-        if (e != hipSuccess) {
-            scratch[dev] = nullptr;
-            return hip_fail(e, "hipHostMalloc(extract_sync words)");
-        }
-    }
-    volatile uint32_t *words = scratch[dev];
-    const int rc = lsb_extract(stego, n, k, msg_out, out_cap, scratch[dev], (int32_t *)(scratch[dev] + 1), stream);
+    if (dev < 0 || dev >= kWaitDevices) return fail(LSB_E_ARG, "lsb_extract_sync: device %d not supported", dev);
+    WaitLine *words = g_wait[dev].take([&e](size_t bytes) {
+        void *page = nullptr;
+        e = hipHostMalloc(&page, bytes, hipHostMallocDefault);
+        return e == hipSuccess ? page : nullptr;
+    });
+    if (!words) return hip_fail(e, "hipHostMalloc(extract_sync words)");
+    const int rc = lsb_extract(stego, n, k, msg_out, out_cap, &words->len, &words->status, stream);
+    // After a HIP error a kernel may be left that still writes its words: they
+    // are not handed out again.
+    if (rc != LSB_OK && rc != LSB_E_HIP) g_wait[dev].give(words);
     if (rc != LSB_OK) return rc;
     e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    const uint32_t len = words[0];
-    const int status = (int)(int32_t)words[1];
+    const uint32_t len = *(volatile uint32_t *)&words->len;
+    const int status = *(volatile int32_t *)&words->status;
+    g_wait[dev].give(words);
     if (len_out_host) *len_out_host = len;
     if (status != LSB_OK)
         fail(status, "lsb_extract_sync: %s (decoded length %u)",
