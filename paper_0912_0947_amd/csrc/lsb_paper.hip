@@ -71,6 +71,21 @@ struct PaperExtract {
     static constexpr RowFn fn[2] = {lsb_paper_extract_units_kernel<C, false>, lsb_paper_extract_units_kernel<C, true>};
 };
 
+// Largest data chunk per row staged in LDS by the row kernel.
+static constexpr uint64_t kPaperRowChunkMax = 60 * 1024;
+static_assert(paper_row_lds_bytes(kPaperRowChunkMax) <= 64 * 1024, "row kernel LDS within 64 KiB");
+
+// Whether the row kernel takes an embed of `rows` rows of another channel count
+// than 1, 3, 4: aligned rows whose chunk fits the LDS, of at least 64 vectors (a
+// quarter of a block's threads; 1000 rows of 512 x 2 bytes 5.1 us against 5.9 by
+// the grid-stride kernel, 10,000 of them 12.1 against 11.6, 10,000 rows of 256 x 2
+// bytes 11.9 against 7.8), and at least one data-carrying row per CU (512 x 512 x
+// 64 in place: 154 such rows 10.2 against 7.4 us, 512 rows 14.9 against 15.8).
+static bool paper_row_kernel(const PaperSpan &p, uint64_t rows) {
+    return (((uintptr_t)p.src | (uintptr_t)p.dst | p.rowbytes) & 15u) == 0 && p.q + 4 <= kPaperRowChunkMax &&
+           p.rowbytes >= 1024 && p.len >= (uint64_t)device_cus() * p.q && rows <= 0xFFFFFFFFull / 256;
+}
+
 static int launched(const char *what) {
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? LSB_OK : hip_fail(e, what);
@@ -116,11 +131,17 @@ int lsb_paper_embed(const uint8_t *cover, uint8_t *stego, uint32_t h, uint32_t w
         const RowFn *fn = c == 1 ? PaperEmbed<1>::fn[a] : (c == 3 ? PaperEmbed<3>::fn[a] : PaperEmbed<4>::fn[a]);
         if (launch_rows(fn, p, units, rows, 2, (hipStream_t)stream)) return launched("paper embed kernel launch");
     }
+    hipEvent_t e0, e1;
+    if ((c == 2 || c > 4) && paper_row_kernel(p, rows)) {
+        take_launch_events(&e0, &e1);
+        hipExtLaunchKernelGGL(lsb_paper_embed_rows_kernel, dim3((unsigned)rows), dim3(256),
+                              (size_t)paper_row_lds_bytes(p.q), (hipStream_t)stream, e0, e1, 0, p);
+        return launched("paper row embed kernel launch");
+    }
     const uint64_t items = vec ? ceil_div(n, 16) : n;
     uint64_t blocks = ceil_div(items, 256);
     const uint64_t cap = (uint64_t)device_cus() * 16;
     if (blocks > cap) blocks = cap;
-    hipEvent_t e0, e1;
     take_launch_events(&e0, &e1);
     if (vec)
         hipExtLaunchKernelGGL(lsb_paper_embed_kernel<true>, dim3((unsigned)blocks), dim3(256), 0,

@@ -148,3 +148,34 @@ def test_row_units(w, c):
         buf = to_dev(cover, pad_before=off, pad_after=16)
         api.paper_embed(buf, h, w, c, plane, to_dev(data), out=buf)
         assert_bytes_equal(to_host(buf), want, "in place " + tag)
+
+
+@pytest.mark.parametrize("c,w,h", [(2, 504, 300), (2, 512, 300), (5, 208, 257), (8, 4096, 259), (17, 64, 300),
+                                   (2, 4 * (61440 - 4), 257), (2, 4 * (61440 - 4) + 8, 257)])
+def test_row_kernel_of_other_channel_counts(c, w, h):
+    """Channel counts without row units: rows of 64 vectors and the width
+    below, rows of many block steps, the largest data chunk that a block stages
+    (61,440 bytes with 4 to spare) and the first width past it; a data pointer
+    off a dword boundary, short last rows around one data row per CU, rows
+    without data, and in place with the bytes around it."""
+    q = w // 4
+    cap = oracle.paper_capacity(h, w)
+    assert cap > 256 * q
+    cover = inputs.random_bytes(h * w * c, 1361, w, c)
+    lens = (cap, 256 * q + 1) if w > 4096 else (cap, 256 * q + 1, 256 * q, 256 * q - 1, 0)
+    for dm, ln in enumerate(lens):
+        plane, dm = (dm + c - 1) % c, dm % 4
+        data = inputs.random_bytes(ln, 1362, w, c, dm)
+        rc, want = oracle.paper_embed(cover, h, w, c, plane, data)
+        assert rc == 0
+        tag = "c=%d w=%d plane=%d len=%d dm=%d" % (c, w, plane, ln, dm)
+        big = to_dev(np.full(cover.size + 32, 0x77, np.uint8))
+        st = big[16:16 + cover.size]
+        api.paper_embed(to_dev(cover), h, w, c, plane, to_dev(data, pad_before=dm, pad_after=3), out=st)
+        got = to_host(big)
+        assert_bytes_equal(got[16:16 + cover.size], want, tag)
+        assert (got[:16] == 0x77).all() and (got[16 + cover.size:] == 0x77).all(), tag
+        st.copy_(torch.from_numpy(cover))
+        api.paper_embed(st, h, w, c, plane, to_dev(data, pad_before=3 - dm), out=st)
+        assert_bytes_equal(to_host(st), want, "in place " + tag)
+        assert_bytes_equal(to_host(api.paper_extract(st, h, w, c, plane, ln)), data, "extract " + tag)
