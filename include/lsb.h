@@ -387,11 +387,12 @@ int lsb_autotune(int op, int k, uint64_t n, uint8_t *cover, uint8_t *stego,
                  double *best_us, void *stream);
 
 /* Batched-kernel configuration: tile size in 16-byte vectors per embed tile
- * (extract tiles span twice as many; a multiple of 64 in [64, 2^30]), the
- * kernel's block/unroll/nontemporal choice and its grid cap (0: a block per
- * tile; a capped grid walks the tiles with a stride).  Blocks need at least
- * 128 threads.  Plans read the tile size at lsb_plan_update and the rest at
- * each run. */
+ * (extract tiles span twice as many, and eight times as many, in blocks of
+ * twice the threads, in extract-only plans of large jobs; a multiple of 64 in
+ * [64, 2^30]), the kernel's block/unroll/nontemporal choice and its grid cap
+ * (0: a block per tile; a capped grid walks the tiles with a stride).  Blocks
+ * need at least 128 threads.  Plans read the tile size at lsb_plan_update and
+ * the rest at each run. */
 int lsb_batch_tune_get(lsb_launch_cfg *cfg, int64_t *tile_vectors);
 int lsb_batch_tune_set(const lsb_launch_cfg *cfg, int64_t tile_vectors);
 

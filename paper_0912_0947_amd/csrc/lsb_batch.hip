@@ -4,8 +4,9 @@
 // The paper loops on the host over the rows of an image (Section VI steps
 // 4-5 split the data across rows; Section VII steps 3-4 likewise), paying a
 // copy and a launch per row.  Here every cover of a batch is a job, each job
-// is cut into tiles of T 16-byte vectors (2T for extract jobs), and one launch
-// has a block per tile, which finds its job through a map from tiles to jobs.  Tile t of a job starts 16*T*t fields after the job's first field, a
+// is cut into tiles of T 16-byte vectors (a multiple of T for extract jobs), and
+// one launch has a block per tile, which finds its job through a map from tiles
+// to jobs.  Tile t of a job starts 16*T*t fields after the job's first field, a
 // whole number of stream bytes, so no two tiles of a job share an output
 // byte.  A job is a whole cover with its length header or a raw slice
 // [t0, t0 + n) of a longer logical cover; slices of one stream may be spread
@@ -59,6 +60,8 @@ struct TableInfo {
     bool has_empty = false;  // some job has no tile: the kernel sweeps the table for them
     int cls = 0;             // 1 + 8*op + (k-1) when every job shares (op, k); kCls*AnyK; else 0
     int map_shift = 0;
+    uint64_t extract_vectors = 0;  // per extract tile
+    bool large_extracts = false;   // extract-only, of large jobs: large tiles and blocks
     size_t used_bytes = 0;   // records, first tile ids and the map's used entries
 };
 
@@ -141,6 +144,24 @@ static int validate_jobs(const lsb_job *jobs, int n_jobs, int op_mode) {
     return LSB_OK;
 }
 
+// Extract tiles, in embed tiles.  An extract moves about half the bytes of an
+// embed (no stego write), so its tile covers twice the vectors to carry the same
+// traffic per job lookup: one step of a block.  Plans of extracts whose jobs are
+// large take tiles of eight instead, two steps of blocks of twice the threads:
+// fewer lookups and header decodes, and longer runs of one job per XCD.  By
+// persistent blocks, as before the block per tile / tiles of two / of eight, us:
+// 4096 covers of 35.7 GB 4071 / 4278 / 3899, 600 frames of 1080p 358 / 376 / 347,
+// 120 frames 86 / 81 / 75, 256 covers of 64..4096 px 242 / 249 / 232.  Below four large tiles a job on average the last
+// tile's idle share costs more (4096 covers of 64..256 px 44 against 52; 1024 jobs
+// of 16,384 vectors 71.2 against 68.0, of 8,192 70.8 against 69.2), and below 1024
+// large tiles in all the chip is not filled (8 frames of 1080p 11.7 against 12.9, 16
+// frames 17.6 against 16.6; one job of 2^20 vectors 10.7 against 11.3, of 2^22 19.4
+// against 18.7).
+constexpr uint64_t kExtractTile = 2, kLargeTile = 8;
+static bool large_jobs(uint64_t vectors, uint64_t jobs, uint64_t tv) {
+    return vectors >= 4 * kLargeTile * tv * jobs && vectors >= 1024 * kLargeTile * tv;
+}
+
 // Fill a job table (records, first tile ids, map) at `host` for validated
 // jobs: per-job status for work the host can already refuse, tile counts and
 // their exclusive prefix, the kernel class.
@@ -149,7 +170,7 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
     DevJob *d = (DevJob *)host;
     uint64_t *first = (uint64_t *)(host + lay.first_off);
     TableInfo t;
-    uint64_t tiles = 0;
+    uint64_t total = 0;  // vectors of all jobs
     for (int i = 0; i < n_jobs; ++i) {
         const lsb_job &J = jobs[i];
         const uint8_t op = op_mode == LSB_OP_MIXED ? J.op : (uint8_t)op_mode;
@@ -164,7 +185,6 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
         D.len = D.raw ? 0 : J.len;  // what the kernel reports in len_dev
         D.k = J.k;
         D.op = op;
-        first[i] = tiles;
         D.status = LSB_OK;
         uint64_t vectors = ceil_div(J.n, 16);
         if (D.raw) {
@@ -202,11 +222,15 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
             if (v_stream < vectors) vectors = v_stream;
             if ((uint64_t)J.k * J.n < 32) vectors = 0;
         }
-        // an extract tile moves about half the bytes of an embed tile (no
-        // stego write), so it covers twice the vectors to carry the same
-        // traffic per job lookup
-        const uint64_t jtv = op == LSB_OP_EMBED ? (uint64_t)tv : 2 * (uint64_t)tv;
-        const uint64_t jt = ceil_div(vectors, jtv);
+        D.vectors = vectors;
+        total += vectors;
+    }
+    t.large_extracts = !t.has_embed && large_jobs(total, (uint64_t)n_jobs, (uint64_t)tv);
+    t.extract_vectors = (t.large_extracts ? kLargeTile : kExtractTile) * (uint64_t)tv;
+    uint64_t tiles = 0;
+    for (int i = 0; i < n_jobs; ++i) {
+        first[i] = tiles;
+        const uint64_t jt = ceil_div(d[i].vectors, d[i].op == LSB_OP_EMBED ? (uint64_t)tv : t.extract_vectors);
         t.has_empty |= jt == 0;
         tiles += jt;
     }
@@ -233,8 +257,8 @@ static TableInfo fill_table(const lsb_job *jobs, int n_jobs, int op_mode, int64_
 
 // One block per tile, capped at blocks_per_cu blocks per CU (0: no cap) and at
 // the 2^32 - 1 threads of a launch.
-static unsigned main_grid_for(const lsb_launch_cfg &cfg, uint64_t total_tiles) {
-    uint64_t cap = 0xFFFFFFFFull / (uint64_t)cfg.block;
+static unsigned main_grid_for(const lsb_launch_cfg &cfg, uint64_t block, uint64_t total_tiles) {
+    uint64_t cap = 0xFFFFFFFFull / block;
     if (cfg.blocks_per_cu > 0) cap = std::min(cap, (uint64_t)cfg.blocks_per_cu * (uint64_t)device_cus());
     return (unsigned)std::min(cap, std::max<uint64_t>(total_tiles, 1));
 }
@@ -251,16 +275,18 @@ static hipError_t launch_batch(const lsb_launch_cfg &cfg, const TableInfo &t, in
     a.map_shift = t.map_shift;
     a.n_jobs = (uint64_t)n_jobs;
     a.total_tiles = t.tiles;
-    a.tile_vectors = (uint64_t)tv;
+    a.embed_vectors = (uint64_t)tv;
+    a.extract_vectors = t.extract_vectors;
     a.cover_arena = cover_arena;
     a.stego_arena = stego_arena;
     a.msg_arena = msg_arena;
     a.len_dev = len_dev;
     a.status_dev = status_dev;
     a.empty_jobs = t.has_empty;
+    const unsigned block = (unsigned)(t.large_extracts ? std::min(2 * cfg.block, 1024) : cfg.block);
     void *argv[] = {&a};
     return hipLaunchKernel((const void *)batch_fn(cfg.unroll, cfg.nontemporal, t.cls, t.has_raw),
-                           dim3(main_grid_for(cfg, t.tiles)), dim3(cfg.block), argv, 0, st);
+                           dim3(main_grid_for(cfg, block, t.tiles)), dim3(block), argv, 0, st);
 }
 
 static int64_t batch_tile_vectors() {

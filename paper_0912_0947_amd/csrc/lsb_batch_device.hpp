@@ -15,7 +15,7 @@ struct DevJob {
     uint64_t cover_off, stego_off, msg_off, n;
     uint64_t cap_bits;  // header extract: msg_cap; raw: end bit (embed: stream_bits, extract: e)
     uint64_t t0;        // raw: logical field index of buffer byte 0; header jobs: 0
-    uint64_t pad;
+    uint64_t vectors;   // vectors that a run may have to visit (host: tile counts)
     uint32_t len;
     uint8_t k, op;
     int8_t status;  // host-validated status; header extract: decoded on device
@@ -52,7 +52,8 @@ struct BatchArgs {
     const DevJob *jobs;
     const uint64_t *first;
     const uint32_t *map;
-    uint64_t n_jobs, total_tiles, tile_vectors;
+    uint64_t n_jobs, total_tiles;
+    uint64_t embed_vectors, extract_vectors;  // per tile of either kind
     const uint8_t *cover_arena;
     uint8_t *stego_arena, *msg_arena;
     uint32_t *len_dev;
@@ -256,26 +257,31 @@ __device__ __forceinline__ uint64_t find_job(const BatchArgs &a, uint64_t t, uin
     return j;
 }
 
+// Consecutive tiles that one XCD takes (see the kernel).
+constexpr uint32_t kTileRun = 32;
+
 // One block per tile: each wave finds the tile's job through the map and
 // streams its share of the tile.  HBM bounds it, as the plain kernels: blocks
 // of other tiles stream while one looks its job up, and a wave ends after its
-// last store without waiting for it.  Tiles go to the XCDs in runs of 16
-// (xcd_run_block): neighbours share lines at their ends, the table entries and
-// an L2 (extract of one 1.6 GB job at k = 1: 353 us in launch order, 309-314
-// us in runs).  A grid capped below the tile count walks the tiles with a
-// stride.  Embed + extract, against persistent blocks whose producer wave took
-// tiles from one counter and handed them to 15 workers: 4096 covers of
-// 64..256 px 216 -> 140 us, 256 covers of 64..4096 px 940 -> 886 us (6.2
-// TB/s), 120 frames of 1080p 340 -> 317 us.  The tile is one step of the
-// block: with two steps the second waits for the first one's stores (256
-// covers' embed 646 us at 512 vectors a tile, 678 us at 1024).
+// last store without waiting for it.  Tiles go to the XCDs in runs of kTileRun
+// (xcd_run_block): neighbours share lines at their ends, the table entries and an
+// L2, and an XCD touches fewer memory pages at a time.  35.7 GB in 4096 covers,
+// us: runs of 16, 32, 64, 128 extract 4049, 3899, 3906, 4001, embed 11,690,
+// 11,530, 11,650, 11,520; launch order extracts a sixth slower than runs of 16.
+// A grid capped below the tile count walks the tiles with a stride.  Embed +
+// extract passes, against persistent blocks whose producer wave took tiles from
+// one counter and handed them to 15 workers: 4096 covers of 64..256 px 225 -> 123
+// us, 256 covers of 64..4096 px 947 -> 890 us (6.2 TB/s), 120 frames of 1080p 345
+// -> 320 us.  An embed tile is one step of the block: with two steps the second
+// waits for the first one's stores (256 covers' embed 646 us at 512 vectors a tile,
+// 678 us at 1024); extracts store little, so theirs may take two (lsb_batch.hip).
 template <int UNR, bool NT, int CLS, bool RAW>
 __global__ void __launch_bounds__(1024, (batch_min_waves<UNR, CLS, RAW>())) lsb_batch_kernel(BatchArgs a) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = uniform32(threadIdx.x >> 6);
     const uint32_t waves = blockDim.x >> 6;
     if (a.empty_jobs) report_empty_jobs(a);
-    for (uint64_t t = xcd_run_block(blockIdx.x, gridDim.x); t < a.total_tiles; t += gridDim.x) {
+    for (uint64_t t = xcd_run_block<kTileRun>(blockIdx.x, gridDim.x); t < a.total_tiles; t += gridDim.x) {
         uint64_t first_tile;
         const uint64_t j = find_job(a, t, lane, &first_tile);
         DevJob J;
@@ -291,8 +297,7 @@ __global__ void __launch_bounds__(1024, (batch_min_waves<UNR, CLS, RAW>())) lsb_
             a.status_dev[j] = r.status;
         }
         if (r.status != LSB_OK) continue;
-        // an extract tile covers twice the vectors of an embed tile
-        const uint64_t tv = J.op == LSB_OP_EXTRACT ? 2 * a.tile_vectors : a.tile_vectors;
+        const uint64_t tv = J.op == LSB_OP_EXTRACT ? a.extract_vectors : a.embed_vectors;
         run_tile<UNR, NT, CLS, RAW>(J, (t - first_tile) * tv, tv, a.cover_arena, a.stego_arena, a.msg_arena, r.len,
                                     wave, waves, lane);
     }

@@ -549,9 +549,11 @@ __device__ __forceinline__ uint32_t decode_header(const uint8_t *stego, int k, u
 // an L2, and the XCDs still interleave at 16-block granularity (handing each
 // XCD one contiguous eighth removed the shared lines too, but made every
 // XCD stream its own distant region and slowed the grid-stride launches).
-// Blocks past the last whole round of 128 keep their index.
+// Blocks past the last whole round of 128 keep their index.  (The batched
+// kernel takes longer runs, kRun.)
+template <uint32_t kRun = 16>
 __device__ __forceinline__ uint32_t xcd_run_block(uint32_t b, uint32_t grid) {
-    constexpr uint32_t kXcds = 8, kRun = 16, kRound = kXcds * kRun;
+    constexpr uint32_t kXcds = 8, kRound = kXcds * kRun;
     if (b >= grid / kRound * kRound) return b;
     const uint32_t x = b % kXcds, slot = b / kXcds;
     return (slot / kRun) * kRound + x * kRun + slot % kRun;
