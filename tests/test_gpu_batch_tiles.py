@@ -1,13 +1,13 @@
-"""Tiles of batched plans: the tile size that plans of large extracts take, with
-small tiles, so that small covers reach it; results against the oracle byte for
-byte."""
+"""Tiles of batched plans: jobs far behind the map entry that finds them, and
+the tile size that plans of large extracts take.  Small tiles, so that small
+covers reach both; results against the oracle byte for byte."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_0912_0947_amd import batch, inputs
-from paper_0912_0947_amd._lib import JOB_RAW, OK, OP_EXTRACT
+from paper_0912_0947_amd._lib import E_CAPACITY, JOB_RAW, OK, OP_EMBED, OP_EXTRACT
 
 from gpu_helpers import DEV, assert_bytes_equal, to_host
 
@@ -19,6 +19,73 @@ def restore_tiles():
     saved = batch.tune_state()
     yield
     batch.tune_restore(saved)
+
+
+def _tile_table(tiles):
+    """First tile ids, map shift and map of a job table, as the library lays
+    them out: the smallest shift whose map fits 4 entries per job plus 4096."""
+    first = np.concatenate([[0], np.cumsum(tiles)])
+    shift = 0
+    while first[-1] >> shift >= 4 * len(tiles) + 4096:
+        shift += 1
+    at = np.arange(((first[-1] - 1) >> shift) + 1) << shift
+    return first, shift, np.searchsorted(first[:-1], at, side="right") - 1
+
+
+@pytest.mark.parametrize("big_first", [True, False])
+def test_jobs_far_behind_their_map_entry(big_first, restore_tiles):
+    """A map entry names the job of its first tile; the others of its tiles
+    look on from there, seven jobs at once and then 64 at a time.  A cover of
+    many tiles makes entries of eight tiles or more, and runs of jobs of one
+    tile and of jobs without tiles (over capacity) put jobs 7 to several
+    hundred places behind their entry's.  Every stego against the oracle."""
+    batch.tune_set(128, 1, 0, 0, 64)
+    g = inputs.rng(4481, int(big_first))
+    big = 48 << 20
+    n, empty = [], []
+
+    def run(count, size, none):
+        n.extend(int(x) for x in (g.integers(16, 100, size=count) if none else g.integers(40, size, size=count)))
+        empty.extend([none] * count)
+
+    for gap in (1, 6, 7, 8, 9, 62, 63, 64, 65, 70, 71, 72, 73, 127, 128, 129, 200, 321):
+        run(int(g.integers(1, 12)), 1024, False)  # one tile each
+        run(gap, 0, True)
+        run(1, 3000, False)
+    run(40, 1024, False)
+    n.insert(0 if big_first else len(n), big + 77)
+    empty.insert(0 if big_first else len(empty), False)
+    n, empty = np.array(n), np.array(empty)
+    tiles = np.where(empty, 0, -(-(-(-n // 16)) // 64))
+    first, shift, entry = _tile_table(tiles)
+    small = np.arange(first[-1])[first[-1] - 400:] if big_first else np.arange(400)
+    step = np.searchsorted(first[:-1], small, side="right") - 1 - entry[small >> shift]
+    assert shift >= 3 and (step == 7).any() and ((step > 7) & (step < 71)).any() and (step > 135).any(), (shift, step.max())
+    jobs = batch.make_jobs(n.size)
+    offs = np.concatenate([[0], np.cumsum([batch.align_up(int(x)) for x in n])])
+    jobs["cover_off"] = jobs["stego_off"] = offs[:-1]
+    jobs["n"], jobs["k"], jobs["op"] = n, 1 + np.arange(n.size) % 8, OP_EMBED
+    caps = np.array([oracle.capacity(int(a), int(b)) for a, b in zip(n, jobs["k"])])
+    jobs["len"] = np.where(empty, np.maximum(caps, 0) + 1, np.clip(caps - 1, 0, 4000))
+    cover = inputs.random_bytes(int(offs[-1]), 4482)
+    msg = inputs.random_bytes(4096, 4483)  # every job reads the same message bytes
+    cover_d, msg_d = torch.from_numpy(cover).to(DEV), torch.from_numpy(msg).to(DEV)
+    stego_d = torch.full_like(cover_d, 0x5A)
+    status = torch.full((n.size,), 99, dtype=torch.int32, device=DEV)
+    plan = batch.Plan(n.size, OP_EMBED, jobs)
+    try:
+        assert plan.tiles == first[-1]
+        plan.embed_batch(cover_d, stego_d, msg_d, status)
+        got, st = to_host(stego_d), status.cpu().numpy()
+    finally:
+        plan.close()
+    assert (st == np.where(empty, E_CAPACITY, OK)).all()
+    want = np.full_like(cover, 0x5A)
+    for i in np.nonzero(~empty)[0]:
+        o, m = int(offs[i]), int(n[i])
+        rc, want[o:o + m] = oracle.embed(cover[o:o + m], msg[:int(jobs["len"][i])], int(jobs["k"][i]))
+        assert rc == OK
+    assert_bytes_equal(got, want, "jobs behind their map entry")
 
 
 @pytest.mark.parametrize("block", [128, 1024])
