@@ -160,8 +160,10 @@ int lsb_paper_extract(const uint8_t *stego, uint32_t h, uint32_t w,
  * the bytes p*c + plane of an HWC image of `pixels` pixels, in raster order;
  * stream, header, bit order and errors as lsb_embed / lsb_extract, with the
  * capacity lsb_capacity(pixels, k).  lsb_embed_plane copies the other bytes
- * (stego == cover: in place, only plane bytes are rewritten).  LSB_E_ARG
- * also for plane >= c, pixels > 2^48 or c > 65536.
+ * (stego == cover: in place, only plane bytes change; images of up to 4
+ * channels on a 16-byte boundary are rewritten in whole vectors, so their
+ * planes are embedded one after another, others may be embedded at once).
+ * LSB_E_ARG also for plane >= c, pixels > 2^48 or c > 65536.
  */
 int lsb_embed_plane(const uint8_t *cover, uint8_t *stego, uint64_t pixels,
                     uint32_t c, uint32_t plane, const uint8_t *msg,

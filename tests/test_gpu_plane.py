@@ -188,3 +188,26 @@ def test_access_kinds_by_size(h, w):
     stego = api.paper_embed(cover_d, h, w, c, plane, to_dev(data))
     assert_bytes_equal(to_host(stego), want, "paper embed")
     assert_bytes_equal(to_host(api.paper_extract(stego, h, w, c, plane, data.size)), data, "paper extract")
+
+
+@pytest.mark.parametrize("c", [2, 3, 4])
+def test_planes_of_one_image_at_once(c):
+    """In place on an image behind a file header (54 bytes), only plane bytes
+    are written: every plane embedded at the same time, each on its own
+    stream, gives the planes embedded one after another."""
+    pixels, off, k = 500_003, 54, 2
+    cover = inputs.random_bytes(pixels * c, 1651, c)
+    msgs = [inputs.random_bytes(oracle.capacity(pixels, k) - 5 * p, 1652, c, p) for p in range(c)]
+    want = cover
+    for p in range(c):
+        rc, want = oracle.embed_plane(want, c, p, msgs[p], k)
+        assert rc == OK
+    msgs_d = [to_dev(m) for m in msgs]
+    streams = [torch.cuda.Stream() for _ in range(c)]  # default priority
+    for rep in range(5):
+        img = to_dev(cover, pad_before=off, pad_after=16)
+        torch.cuda.synchronize()
+        for p in range(c):
+            api.embed_plane(img, c, p, msgs_d[p], k, out=img, stream=streams[p])
+        torch.cuda.synchronize()
+        assert_bytes_equal(to_host(img), want, "%d planes at once, repetition %d" % (c, rep))
