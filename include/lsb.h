@@ -283,7 +283,8 @@ int lsb_plan_create(lsb_plan **plan, const lsb_job *jobs_host, int n_jobs, int o
  * offsets, flags or raw-slice alignment is LSB_E_ARG for the whole call; a
  * header embed job whose len exceeds its
  * capacity is not an error of the call: it gets status LSB_E_CAPACITY and no
- * work.  Waits for the plan's previous run to have read the job table. */
+ * work.  Waits for the plan's previous run to be over; what that run wrote to
+ * host memory is visible only once its stream has been waited for. */
 int lsb_plan_update(lsb_plan *plan, const lsb_job *jobs_host, int n_jobs);
 
 /* Run every job of the plan on `stream`.  Every run of a plan uses the

@@ -315,13 +315,19 @@ int lsb_plan_create(lsb_plan **out, const lsb_job *jobs, int n_jobs, int op) {
     e = hipMalloc((void **)&p->dev, p->table_bytes);
     if (e != hipSuccess)
         return (void)hipHostFree(p->host), delete p, fail(LSB_E_NOMEM, "lsb_plan_create: hipMalloc failed");
-    // Nothing the host or another device reads hangs on this event (it orders
-    // later uploads and runs on this device, and the freeing of the table), so
-    // it needs no system-wide fence, which the next run on the stream would
-    // wait for: 4096 covers of 64..256 px, embed + extract, 117.3 -> 114.0 us;
-    // 25 frames of 720p 40.8 -> 37.4 us.  (Bound to the kernel as its stop event
-    // it is cheaper still, 111.6 and 35.1 us, but after thousands of runs in
-    // flight the runtime then takes milliseconds to clear the launches.)
+    // The event orders execution only: later runs and uploads on this device
+    // start after the run (whose kernel's own release at its end, device wide,
+    // makes its writes visible to them), an update overwrites the pinned mirror
+    // after the upload has read it, a destroy frees the table after the kernel has
+    // read it.  No memory that the host reads is published by it: results in host
+    // memory become visible through the stream, as lsb.h says, not through an
+    // update or a destroy that waits here.  So it needs no system-wide fence
+    // (without one, device memory may be unseen by the host and by other devices,
+    // by the flag's description), which the next run on the stream would wait for:
+    // 4096 covers of 64..256 px, embed + extract, 117.3 -> 114.0 us; 25 frames of
+    // 720p 40.8 -> 37.4 us.  (Bound to the kernel as its stop event it is cheaper
+    // still, 111.6 and 35.1 us, but after thousands of runs in flight the runtime
+    // then takes milliseconds to clear the launches.)
     e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) return (void)hipFree(p->dev), (void)hipHostFree(p->host), delete p, hip_fail(e, "hipEventCreate");
     memset(p->host, 0, p->table_bytes);
