@@ -1,6 +1,6 @@
 """Autotuning driver: chooses launch shapes per (op, k, size) in embed/extract
-pairs, the large-image workload's in its own sequence, sweeps the batched
-kernel, and stores the winners as JSON next to this file.
+pairs and on cold covers, the large-image workload's in its own sequence, sweeps
+the batched kernel, and stores the winners as JSON next to this file.
 
 ``load()`` installs a stored table into the library (called on import of
 paper_0912_0947_amd.api).  Buckets that were not tuned take the entry of the
@@ -18,8 +18,8 @@ import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "tune_gfx950.json")
-# One size per bucket, in its middle or the size of a workload that falls into it.
-SIZES = [{19: 786432, 22: 6220800, 27: 201326592}.get(b, 3 << (b - 1)) for b in range(12, 31)]
+# One size per bucket from 2 MB on, in its middle or the size of a workload that falls into it.
+SIZES = [{22: 6220800, 27: 201326592}.get(b, 3 << (b - 1)) for b in range(21, 31)]
 KS = range(1, 9)
 # Buffers from here up take streaming (non-temporal) shapes only: one cover
 # and its stego no longer fit the 256 MB last-level cache.
@@ -75,79 +75,226 @@ def load(handle=None, path: str = TABLE) -> bool:
     return True
 
 
-def tune_pair(k: int, n: int, sets, reps: int = 4, finals: int = 12, log=print):
-    """Shapes of embed and extract for (k, n), chosen together: each candidate
-    of one operation is timed in passes that embed into a stego buffer and
-    extract from it, over the buffer sets in turn, with the other operation at
-    its best shape so far.  The score is the sum of both launches (each timed
-    by events bound to its kernel), so a shape that leaves the memory system
-    in a state the next kernel pays for, or its output in the caches, is
-    charged or credited for it.  Candidates take turns (slow drift of the
-    device affects all alike); the best ``finals`` are timed again, four times
-    as often.  ``sets`` holds (cover, stego, msg, out, len_status) per set.
-    Returns the two table entries."""
+class Timer:
+    """Launches of embed and extract over arenas of covers, stegos and
+    messages, each timed by events bound to its kernel."""
+
+    def __init__(self, arena: int = 6 << 30):
+        import torch
+
+        from . import api, inputs
+        from ._lib import lib
+
+        dev = torch.device("cuda:0")
+        self.lib, self.arena, self.at = lib(), arena, 0
+        self.cover, self.stego = (torch.empty(arena, dtype=torch.uint8, device=dev) for _ in range(2))
+        self.msg, self.out = (torch.empty(arena // 4, dtype=torch.uint8, device=dev) for _ in range(2))
+        inputs.fill_uniform(self.cover, 13)
+        inputs.fill_uniform(self.msg, 23)
+        self.state = torch.zeros(2, dtype=torch.int32, device=dev)
+        self.ev = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(64)]
+        for pair in self.ev:  # create the HIP events (torch records lazily); the library re-records them
+            for e in pair:
+                e.record()
+        torch.cuda.synchronize()
+        self.run = {api.OP_EMBED: self._embed, api.OP_EXTRACT: self._extract}
+
+    def use(self, k: int, n: int) -> None:
+        """Covers of n bytes at k, every stego of the arena a valid one."""
+        from . import api
+
+        self.k, self.n, self.cap = k, n, min(api.capacity(n, k), 1 << 30)
+        self.step, self.mstep = -(-n // 256) * 256, -(-self.cap // 256) * 256
+        self.slots, self.mslots = self.arena // self.step, self.arena // 4 // self.mstep
+        for i in range(self.slots):
+            self._embed(i, None)
+
+    def _embed(self, i, ev):
+        from . import api
+
+        c, m = i % self.slots * self.step, i % self.mslots * self.mstep
+        if ev:
+            self.lib.lsb_time_next_launch(*ev)
+        api.embed(self.cover[c:c + self.n], self.msg[m:m + self.cap], self.k, out=self.stego[c:c + self.n])
+
+    def _extract(self, i, ev):
+        from . import api
+
+        c, m = i % self.slots * self.step, i % self.mslots * self.mstep
+        if ev:
+            self.lib.lsb_time_next_launch(*ev)
+        api.extract(self.stego[c:c + self.n], self.k, out=self.out[m:m + self.cap], len_status=self.state)
+
+    def hot(self, passes: int):
+        """(embed, extract) us of passes that embed into one of three buffer
+        sets in turn and at once extract from it."""
+        import torch
+
+        for i in range(passes):
+            self._embed(i % 3, self.ev[2 * i])
+            self._extract(i % 3, self.ev[2 * i + 1])
+        torch.cuda.synchronize()
+        us = [a.elapsed_time(b) * 1e3 for a, b in self.ev[:2 * passes]]
+        return list(zip(us[::2], us[1::2]))
+
+    def cold(self, op: int, launches: int):
+        """us of launches on covers that no cache holds: each a seventh of the
+        arena behind the one before."""
+        import torch
+
+        for i in range(launches):
+            self.at += max(1, self.slots // 7)
+            self.run[op](self.at, self.ev[i])
+        torch.cuda.synchronize()
+        return [a.elapsed_time(b) * 1e3 for a, b in self.ev[:launches]]
+
+    def check(self) -> None:
+        """The last extract returned its message."""
+        assert self.state.cpu().tolist() == [self.cap, 0], (self.k, self.n, self.state.cpu().tolist())
+
+
+def _install(op: int, k: int, n: int, c: dict) -> None:
+    from . import api
+
+    api.tune_set(op, k, bucket(n), c["block"], c["unroll"], c["blocks_per_cu"], c["nontemporal"], c["pack"], c["order"])
+
+
+def _shapes(nts, orders, packs=(0,)):
+    """Candidate shapes, plain ones first: shapes that tie take the first."""
+    return [{"block": b, "unroll": u, "blocks_per_cu": c, "nontemporal": nt, "pack": pk, "order": o}
+            for pk in packs for c in CAPS for o in orders for u in (2, 1, 4) for b in BLOCKS for nt in nts]
+
+
+def _choose(best_of, hot, cold):
+    """Index of the shape with the lowest cold time among those within 2 % of
+    the best hot time; within 1 % of that, the first."""
+    near = [i for i in best_of if hot[i] <= 1.02 * min(hot[j] for j in best_of)]
+    low = min(cold[i] for i in near)
+    return min(i for i in near if cold[i] <= 1.01 * low)
+
+
+def tune_pair(timer: Timer, k: int, n: int, reps: int = 4, finals: int = 24, log=print):
+    """Shapes of embed and extract for (k, n), each chosen in two views.  Hot:
+    passes that embed into a stego buffer and extract from it, over three buffer
+    sets in turn, with the other operation at its best shape so far; the sum of
+    both launches, so a shape that leaves the memory system in a state the next
+    kernel pays for, or its output in the caches, is charged or credited for it.
+    Cold: single launches on covers that no cache holds, as a loop over an
+    archive sees them.  Candidates take turns (slow drift of the device affects
+    all alike); the best ``finals`` hot ones are timed again, hot and cold, and
+    among those that are as good hot the best cold one is taken (either view
+    alone picks shapes that the other finds up to a quarter slower).  Returns
+    the two table entries."""
     import statistics
 
-    import torch
-
     from . import api
-    from ._lib import lib
 
-    L = lib()
-    cap = api.capacity(n, k)
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
-    for e in ev:  # create the HIP events (torch records lazily); the library re-records them
-        e.record()
-    torch.cuda.synchronize()
-    best = {op: {"block": 256, "unroll": 2, "blocks_per_cu": 0, "nontemporal": 1, "pack": 0, "order": 0}
-            for op in (api.OP_EMBED, api.OP_EXTRACT)}
-    it = [0]
-
-    def install(op, c):
-        api.tune_set(op, k, bucket(n), c["block"], c["unroll"], c["blocks_per_cu"], c["nontemporal"], c["pack"],
-                     c["order"])
-
-    def one_pass():
-        cover, stego, msg, out, ls = sets[it[0] % len(sets)]
-        it[0] += 1
-        L.lsb_time_next_launch(ev[0], ev[1])
-        api.embed(cover[:n], msg[:cap], k, out=stego[:n])
-        L.lsb_time_next_launch(ev[2], ev[3])
-        api.extract(stego[:n], k, out=out[:cap], len_status=ls)
-        torch.cuda.synchronize()
-        return ev[0].elapsed_time(ev[1]) * 1e3, ev[2].elapsed_time(ev[3]) * 1e3
-
-    def rank(op, cands, rounds):
-        times = [[] for _ in cands]
-        for r in range(rounds + 1):
-            for ci, c in enumerate(cands):
-                install(op, c)
-                t = one_pass()
-                if r:  # round 0 warms every shape up
-                    times[ci].append(t)
-        med = [(statistics.median(e + x for e, x in ts), ci) for ci, ts in enumerate(times)]
-        return sorted(med), times
-
-    entries = {}
+    timer.use(k, n)
     nts = (1,) if n >= STREAM_MIN else (0, 1)
     orders = ORDERS if n >= RUNS_MIN else (0,)
+    first = _shapes((nts[-1],), (0,))[0]
+    best = {api.OP_EMBED: first, api.OP_EXTRACT: first}
+    entries = {}
     for op in (api.OP_EXTRACT, api.OP_EMBED, api.OP_EXTRACT):
         for o in best:
-            install(o, best[o])
-        packs = (0, 1) if (op == api.OP_EXTRACT and k == 1) else (0,)
-        cands = [{"block": b, "unroll": u, "blocks_per_cu": c, "nontemporal": nt, "pack": pk, "order": o}
-                 for nt in nts for o in orders for pk in packs for b in BLOCKS for u in UNROLLS for c in CAPS]
-        order, _ = rank(op, cands, reps)
-        cands = [cands[ci] for _, ci in order[:finals]]
-        order, times = rank(op, cands, 4 * reps)
-        best[op] = cands[order[0][1]]
-        install(op, best[op])
-        us = statistics.median(t[op] for t in times[order[0][1]])
-        entries[op] = {"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": best[op], "us": round(us, 2),
-                       "method": "pair"}
-    log("k=%d n=%d -> embed %s %.1f us, extract %s %.1f us" % (
-        k, n, best[0], entries[0]["us"], best[1], entries[1]["us"]))
+            _install(o, k, n, best[o])
+        cands = _shapes(nts, orders, (0, 1) if op == api.OP_EXTRACT and k == 1 else (0,))
+
+        def turns(indices, rounds, passes, view):
+            times = {i: [] for i in indices}
+            for r in range(rounds + 1):
+                for i in indices:
+                    _install(op, k, n, cands[i])
+                    t = view(passes)
+                    if r:  # round 0 warms every shape up
+                        times[i] += t
+            return times
+
+        hot = turns(range(len(cands)), reps, 1, timer.hot)
+        hot = {i: statistics.median(e + x for e, x in ts) for i, ts in hot.items()}
+        last = sorted(sorted(hot, key=hot.get)[:finals])
+        both = turns(last, reps, 6, timer.hot)
+        cold = turns(last, reps, 6, lambda c: timer.cold(op, c))
+        hot = {i: statistics.median(e + x for e, x in ts) for i, ts in both.items()}
+        cold = {i: statistics.median(ts) for i, ts in cold.items()}
+        i = _choose(last, hot, cold)
+        best[op] = cands[i]
+        _install(op, k, n, best[op])
+        entries[op] = {"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": best[op],
+                       "us": round(statistics.median(t[op] for t in both[i]), 2), "cold_us": round(cold[i], 2),
+                       "method": "hot and cold"}
+    timer.check()
+    log("k=%d n=%d -> %s" % (k, n, ["%s %.1f us hot, %.1f cold" % (list(e["cfg"].values()), e["us"], e["cold_us"])
+                                    for e in entries.values()]))
     return [entries[0], entries[1]]
+
+
+def keep_better(timer: Timer, stored, new, rounds: int = 6, log=print):
+    """Of two pairs of entries of one (k, n), the new one only if it is as good
+    in one view and better in the other by more than measurements differ: both
+    pairs take turns, hot and cold; the sum of both views has to fall by 2 %, and
+    neither view may rise by 2 %."""
+    import statistics
+
+    k, n = new[0]["k"], new[0]["n"]
+    times = [([], []) for _ in range(2)]
+    for r in range(rounds + 1):
+        for pair, (hot, cold) in zip((stored, new), times):
+            for e in pair:
+                _install(e["op"], k, n, e["cfg"])
+            h = [sum(p) for p in timer.hot(8)]
+            c = [sum(p) for p in zip(*(timer.cold(e["op"], 8) for e in pair))]
+            if r:
+                hot += h
+                cold += c
+    (h0, c0), (h1, c1) = [[statistics.median(v) for v in views] for views in times]
+    better = h1 + c1 < 0.98 * (h0 + c0) and h1 < 1.02 * h0 and c1 < 1.02 * c0
+    log("k=%d n=%d stored %.2f hot %.2f cold, new %.2f %.2f -> %s" % (k, n, h0, c0, h1, c1,
+                                                                     "new" if better else "stored"))
+    for e in new if better else stored:
+        _install(e["op"], k, n, e["cfg"])
+    return new if better else stored
+
+
+def tune_small(timer: Timer, log=print):
+    """One shape per operation for every cover below RUNS_MIN and every k: a
+    launch takes 4 us there whatever its shape, to within the spread of a
+    measurement, so a choice per size would be one by noise.  Shapes are ranked
+    by their mean hot and cold times over sizes and k; within 1 % the first is
+    taken.  Returns the entries of the largest bucket below RUNS_MIN, which the
+    smaller ones share."""
+    import statistics
+
+    from . import api
+
+    n_max = 3 << 19
+    sizes = [3 << b for b in range(11, 20, 2)]
+    cands = _shapes((0, 1), (0,))
+    total = {op: [0.0] * len(cands) for op in (api.OP_EMBED, api.OP_EXTRACT)}
+    for n in sizes:
+        for k in (1, 2, 4, 8):
+            timer.use(k, n)
+            for op in total:
+                times = [[] for _ in cands]
+                for r in range(4):
+                    for i, c in enumerate(cands):
+                        _install(op, k, n, c)
+                        t = [p[op] for p in timer.hot(4)], timer.cold(op, 4)
+                        if r:
+                            times[i].append(t)
+                for i, ts in enumerate(times):
+                    total[op][i] += sum(statistics.median(x for t in ts for x in t[view]) for view in (0, 1))
+    entries = []
+    for op, sums in total.items():
+        i = min(i for i, v in enumerate(sums) if v <= 1.01 * min(sums))
+        us = sums[i] / (2 * 4 * len(sizes))
+        log("op=%d below %d bytes -> %s %.2f us (best %.2f, worst %.2f)" % (
+            op, RUNS_MIN, list(cands[i].values()), us, min(sums) / (8 * len(sizes)), max(sums) / (8 * len(sizes))))
+        entries += [{"op": op, "k": k, "bucket": bucket(n_max), "n": n_max, "cfg": cands[i], "us": round(us, 2),
+                     "method": "one shape below 2 MB"} for k in KS]
+        for k in KS:
+            _install(op, k, n_max, cands[i])
+    return entries
 
 
 # The large-image workload: embed then extract at k = 1, 2, 4 on one 8192 x
@@ -237,28 +384,17 @@ def tune_sequence(n: int = SEQUENCE_N, seq=SEQUENCE, reps: int = 7, log=print):
     return entries
 
 
-def tune_plain(reps: int = 4, sizes=SIZES, ks=KS, log=print):
-    import torch
-
-    from . import api, inputs
-
-    dev = torch.device("cuda:0")
-    entries = []
-    biggest = max(sizes)
-    sets = []
-    for j in range(ROT_SETS):
-        cover = torch.empty(biggest, dtype=torch.uint8, device=dev)
-        msg = torch.empty(biggest, dtype=torch.uint8, device=dev)
-        inputs.fill_uniform(cover, 13 + j)
-        inputs.fill_uniform(msg, 23 + j)
-        sets.append((cover, torch.empty(biggest, dtype=torch.uint8, device=dev), msg,
-                     torch.empty(biggest, dtype=torch.uint8, device=dev),
-                     torch.zeros(2, dtype=torch.int32, device=dev)))
+def tune_plain(reps: int = 4, sizes=SIZES, ks=KS, log=print, stored=()):
+    """Entries for every k and size; those in ``stored`` (an earlier table's)
+    stay where the new ones are not measurably better."""
+    timer = Timer()
+    entries = tune_small(timer, log=log)
+    old = {(e["op"], e["k"], e["n"]): e for e in stored}
     for n in sizes:
         for k in ks:
-            entries += tune_pair(k, n, sets, reps=reps, log=log)
-            for _, _, _, _, ls in sets:  # the extracts returned every message
-                assert ls.cpu().tolist() == [api.capacity(n, k), 0], (k, n, ls.cpu().tolist())
+            new = tune_pair(timer, k, n, reps=reps, log=log)
+            had = [old.get((e["op"], k, n)) for e in new]
+            entries += keep_better(timer, had, new, log=log) if all(had) else new
     return entries
 
 
@@ -328,6 +464,8 @@ def main():
     ap.add_argument("--batch", action="store_true", help="also sweep the batched kernel")
     ap.add_argument("--batch-only", action="store_true",
                     help="sweep the batched kernel only; the stored plain-kernel entries stay")
+    ap.add_argument("--below", type=int, default=0,
+                    help="re-choose the plain kernels' shapes of covers below this size only")
     ap.add_argument("--sequence-only", action="store_true",
                     help="re-choose the large-image workload's six launch shapes inside their sequence only")
     ap.add_argument("--out", default=TABLE)
@@ -348,6 +486,16 @@ def main():
         with open(TABLE) as f:
             table = json.load(f)
         table["batch"], table["batch_sweep"] = tune_batch(log=log)
+        with open(args.out, "w") as f:
+            json.dump(table, f, indent=1)
+        log("wrote", args.out)
+        return
+    if args.below:
+        with open(TABLE) as f:
+            table = json.load(f)
+        kept = [e for e in table["entries"] if e["n"] >= args.below]
+        table["entries"] = tune_plain(args.reps, [n for n in SIZES if n < args.below], log=log,
+                                      stored=table["entries"]) + kept
         with open(args.out, "w") as f:
             json.dump(table, f, indent=1)
         log("wrote", args.out)
