@@ -162,7 +162,7 @@ def _install(op: int, k: int, n: int, c: dict) -> None:
 def _shapes(nts, orders, packs=(0,)):
     """Candidate shapes, plain ones first: shapes that tie take the first."""
     return [{"block": b, "unroll": u, "blocks_per_cu": c, "nontemporal": nt, "pack": pk, "order": o}
-            for pk in packs for c in CAPS for o in orders for u in (2, 1, 4) for b in BLOCKS for nt in nts]
+            for pk in packs for c in CAPS for o in orders for u in UNROLLS for b in BLOCKS for nt in nts]
 
 
 def _choose(best_of, hot, cold):
@@ -257,130 +257,49 @@ def keep_better(timer: Timer, stored, new, rounds: int = 6, log=print):
 
 
 def tune_small(timer: Timer, log=print):
-    """One shape per operation for every cover below RUNS_MIN and every k: a
-    launch takes 4 us there whatever its shape, to within the spread of a
-    measurement, so a choice per size would be one by noise.  Shapes are ranked
-    by their mean hot and cold times over sizes and k; within 1 % the first is
-    taken.  Returns the entries of the largest bucket below RUNS_MIN, which the
-    smaller ones share."""
-    import statistics
-
-    from . import api
-
-    n_max = 3 << 19
-    sizes = [3 << b for b in range(11, 20, 2)]
-    cands = _shapes((0, 1), (0,))
-    total = {op: [0.0] * len(cands) for op in (api.OP_EMBED, api.OP_EXTRACT)}
-    for n in sizes:
-        for k in (1, 2, 4, 8):
-            timer.use(k, n)
-            for op in total:
-                times = [[] for _ in cands]
-                for r in range(4):
-                    for i, c in enumerate(cands):
-                        _install(op, k, n, c)
-                        t = [p[op] for p in timer.hot(4)], timer.cold(op, 4)
-                        if r:
-                            times[i].append(t)
-                for i, ts in enumerate(times):
-                    total[op][i] += sum(statistics.median(x for t in ts for x in t[view]) for view in (0, 1))
-    entries = []
-    for op, sums in total.items():
-        i = min(i for i, v in enumerate(sums) if v <= 1.01 * min(sums))
-        us = sums[i] / (2 * 4 * len(sizes))
-        log("op=%d below %d bytes -> %s %.2f us (best %.2f, worst %.2f)" % (
-            op, RUNS_MIN, list(cands[i].values()), us, min(sums) / (8 * len(sizes)), max(sums) / (8 * len(sizes))))
-        entries += [{"op": op, "k": k, "bucket": bucket(n_max), "n": n_max, "cfg": cands[i], "us": round(us, 2),
-                     "method": "one shape below 2 MB"} for k in KS]
-        for k in KS:
-            _install(op, k, n_max, cands[i])
-    return entries
-
-
-# The large-image workload: embed then extract at k = 1, 2, 4 on one 8192 x
-# 8192 x 3 cover, every launch on a buffer the previous ones did not touch.
-SEQUENCE_N = 201326592
-SEQUENCE = ((0, 1), (1, 1), (0, 2), (1, 2), (0, 4), (1, 4))
-
-
-def tune_sequence(n: int = SEQUENCE_N, seq=SEQUENCE, reps: int = 7, log=print):
-    """Choose the shapes of the launches of a workload sequence inside that
-    sequence.  For each member (op, k) in turn every streaming candidate shape
-    is installed for n's bucket and the whole sequence runs reps + 1 times
-    over three rotating buffer sets, the member's launch timed by events bound
-    to it; the lowest median wins before the next member is tuned.
-    Shapes that tie on an idle device can differ by 10 % here, behind the
-    preceding kernels' traffic.  Returns table entries."""
+    """One shape per operation for every cover below RUNS_MIN and every k.  A
+    kernel takes 4 us there by its own events whatever its shape, to within the
+    spread of a measurement, so a choice per size by those would be one by
+    noise; what differs, by up to a microsecond, is an embed and waited extract
+    issued from C (lsb_roundtrip_latency, 14 to 16 us to a hundredth).  Shapes are
+    ranked by its sum over sizes and k, the other operation at the first shape.
+    Returns the entries of the largest bucket below RUNS_MIN, which the smaller
+    ones share."""
+    import ctypes
     import statistics
 
     import torch
 
-    from . import api, inputs
-    from ._lib import lib
+    from . import api
+    from ._lib import check
 
-    L = lib()
-    dev = torch.device("cuda:0")
-    ks = sorted({k for _, k in seq})
-    sets = 3
-    covers = [torch.empty(n, dtype=torch.uint8, device=dev) for _ in range(sets)]
-    for i, c in enumerate(covers):
-        inputs.fill_uniform(c, 31 + i)
-    msgs = {k: torch.empty(api.capacity(n, k), dtype=torch.uint8, device=dev) for k in ks}
-    for k, m in msgs.items():
-        inputs.fill_uniform(m, 41 + k)
-    stegos = {k: [torch.empty(n, dtype=torch.uint8, device=dev) for _ in range(sets)] for k in ks}
-    outs = {k: [torch.empty(msgs[k].numel(), dtype=torch.uint8, device=dev) for _ in range(sets)] for k in ks}
-    ls = torch.zeros((len(ks), sets, 2), dtype=torch.int32, device=dev)
-    for k in ks:
-        for j in range(sets):
-            api.embed(covers[j], msgs[k], k, out=stegos[k][j])
-    torch.cuda.synchronize()
-    it = [0]
-
-    def run_sequence(target, events):
-        j = it[0] % sets
-        jx = (it[0] + 1) % sets
-        it[0] += 1
-        for op, k in seq:
-            if (op, k) == target:
-                L.lsb_time_next_launch(*events)
-            if op == api.OP_EMBED:
-                api.embed(covers[j], msgs[k], k, out=stegos[k][j])
-            else:
-                api.extract(stegos[k][jx], k, out=outs[k][jx], len_status=ls[ks.index(k), jx])
-
+    cands = [c for c in _shapes((0, 1), (0,)) if c["blocks_per_cu"] == 0]
+    points = [(n, k) for n in (4096, 49152, 196608, 786432, 1572864) for k in (1, 2, 5)]
+    med, low = ctypes.c_double(), ctypes.c_double()
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     entries = []
-    ev = (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
-    for e in ev:
-        e.record()
-    torch.cuda.synchronize()
-    for op, k in seq:
-        best = None
-        for order in ORDERS:
-            for block in BLOCKS:
-                for unroll in UNROLLS:
-                    for capb in CAPS:
-                        api.tune_set(op, k, bucket(n), block, unroll, capb, 1, 0, order)
-                        ms = []
-                        for r in range(reps + 1):
-                            run_sequence((op, k), ev)
-                            torch.cuda.synchronize()
-                            if r:
-                                ms.append(ev[0].elapsed_time(ev[1]))
-                        us = statistics.median(ms) * 1e3
-                        if best is None or us < best[1]:
-                            best = ({"block": block, "unroll": unroll, "blocks_per_cu": capb, "nontemporal": 1,
-                                     "pack": 0, "order": order}, us)
-        c = best[0]
-        api.tune_set(op, k, bucket(n), c["block"], c["unroll"], c["blocks_per_cu"], 1, 0, c["order"])
-        entries.append({"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": c, "us": round(best[1], 2),
-                        "method": "sequence"})
-        log("op=%d k=%d n=%d -> %s %.1f us (in the embed/extract sequence)" % (op, k, n, c, best[1]))
-    # every extract of the last pass returned its message
-    st = ls.cpu().numpy()
-    for ki, k in enumerate(ks):
-        for j in range(sets):
-            assert st[ki, j, 1] == 0 and st[ki, j, 0] == msgs[k].numel(), (k, j, st[ki, j])
+    for op in (api.OP_EMBED, api.OP_EXTRACT):
+        total = [0.0] * len(cands)
+        for n, k in points:
+            _install(1 - op, k, n, cands[0])
+            us = [[] for _ in cands]
+            for r in range(4):
+                for i, c in enumerate(cands):
+                    _install(op, k, n, c)
+                    check(timer.lib.lsb_roundtrip_latency(
+                        timer.cover.data_ptr(), timer.stego.data_ptr(), n, timer.msg.data_ptr(), n * k // 16, k,
+                        timer.out.data_ptr(), 300, ctypes.byref(med), ctypes.byref(low), stream))
+                    if r:
+                        us[i].append(med.value)
+            total = [t + statistics.median(u) / len(points) for t, u in zip(total, us)]
+        i = total.index(min(total))
+        log("op=%d below %d bytes -> %s, waited pass %.2f us (worst shape %.2f)" % (
+            op, RUNS_MIN, list(cands[i].values()), total[i], max(total)))
+        n = RUNS_MIN - 1
+        entries += [{"op": op, "k": k, "bucket": bucket(n), "n": n, "cfg": cands[i], "us": round(total[i], 2),
+                     "method": "waited passes below 2 MB"} for k in KS]
+    for e in entries:
+        _install(e["op"], e["k"], e["n"], e["cfg"])
     return entries
 
 
@@ -464,6 +383,7 @@ def main():
     ap.add_argument("--batch", action="store_true", help="also sweep the batched kernel")
     ap.add_argument("--batch-only", action="store_true",
                     help="sweep the batched kernel only; the stored plain-kernel entries stay")
+    ap.add_argument("--small-only", action="store_true", help="re-choose the shapes of covers below 2 MB only")
     ap.add_argument("--below", type=int, default=0,
                     help="re-choose the plain kernels' shapes of covers below this size only")
     ap.add_argument("--sequence-only", action="store_true",
@@ -486,6 +406,14 @@ def main():
         with open(TABLE) as f:
             table = json.load(f)
         table["batch"], table["batch_sweep"] = tune_batch(log=log)
+        with open(args.out, "w") as f:
+            json.dump(table, f, indent=1)
+        log("wrote", args.out)
+        return
+    if args.small_only:
+        with open(TABLE) as f:
+            table = json.load(f)
+        table["entries"] = tune_small(Timer(1 << 28), log=log) + [e for e in table["entries"] if e["n"] >= RUNS_MIN]
         with open(args.out, "w") as f:
             json.dump(table, f, indent=1)
         log("wrote", args.out)
