@@ -237,7 +237,7 @@ def cpu_baseline_threads(cover_np, msgs, threads, min_seconds=1.5, max_steps=4):
 
 
 def bench_batched(api, batch, dev, log_fn, reps=3):
-    """Uneven batch of 4096 covers (about 35 GB): one persistent launch
+    """Uneven batch of 4096 covers (about 35 GB): one launch
     per op against a loop of one plain launch per cover on one stream."""
     import ctypes
 
@@ -619,7 +619,7 @@ def bench_video(api, lib_handle, dev, log_fn, frames=600, h=1080, w=1920):
     device-resident per frame: 600 lsb_embed_raw launches (t0 = f * frame),
     issued from the host and, separately, captured once in a HIP graph;
     device-resident per frame, batched: the 600 frames as raw-slice jobs of
-    one batched plan (one persistent launch); extraction of the stream the
+    one batched plan (one launch); extraction of the stream the
     same three ways (whole clip, 600 raw launches, 600 batched raw jobs);
     host-streamed: the clip in pinned host memory pipelined through a 4-slot
     device ring, frames alternating over two streams that each copy in, embed
@@ -682,8 +682,8 @@ def bench_video(api, lib_handle, dev, log_fn, frames=600, h=1080, w=1920):
     res["device_per_frame_graph"] = {"launches": frames, "ms": round(best * 1e3, 3),
                                      "GBps": round((2 * n + ln + 4) / best / 1e9, 1)}
     del graph
-    # the same frames as raw-slice jobs of one batched plan: one persistent
-    # launch walks every frame (the clip is the cover arena, frame f at f * fb)
+    # the same frames as raw-slice jobs of one batched plan: one
+    # launch covers every frame (the clip is the cover arena, frame f at f * fb)
     jobs = batch.make_jobs(frames)
     jobs["cover_off"] = jobs["stego_off"] = np.arange(frames, dtype=np.uint64) * fb
     jobs["n"], jobs["k"], jobs["flags"] = fb, 1, batch.JOB_RAW

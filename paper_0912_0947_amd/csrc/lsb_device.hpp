@@ -35,10 +35,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Memory forms of a vector, a dword and a short at any byte address: gfx950
 // takes unaligned global accesses of every width (the compiler emits the same
 // instructions as for aligned ones), so buffers need no alignment at all.
-// A 36 MB cover behind a 54-byte file header at k = 2 (embed, then extract):
-// 29 us, against 91 us through the per-byte kernels that misaligned buffers
-// used to take and 26 us aligned.  At 201 MB an offset of 6 bytes costs the
-// embed 3-10 % and the extract 10-20 %, an offset of 8 nothing.
+// A 36 MB cover behind a 54-byte file header at k = 2, embed + extract pass:
+// 23.5 us, against 88 through the per-byte kernels that misaligned buffers used to
+// take.  Kernels at byte 0 / 4 / 54, us: 201 MB k = 1 embed 63.8 / 69.2 / 73.3,
+// extract 35.6 / 34.5 / 44.5, k = 4 78.2 / 77.9 / 77.8 and 45.6 / 45.9 / 50.6; 36 MB
+// k = 2, read from the caches, 12.4 / 12.4 / 13.0 and 7.5 / 9.5 / 12.4; 0.8 MB no
+// difference.
 typedef u32x4 u32x4_any __attribute__((aligned(1)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
 typedef uint16_t u16_any __attribute__((aligned(1)));

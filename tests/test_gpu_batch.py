@@ -1,4 +1,4 @@
-"""GPU parity of the batched (persistent) path.
+"""GPU parity of the batched path.
 
 Each job's result must equal the oracle's and the single-call result, for
 mixed embed/extract batches with invalid jobs, tiny tiles (many tile

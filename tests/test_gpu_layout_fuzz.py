@@ -1,6 +1,6 @@
 """Randomised single-plane and paper-layout calls (hypothesis, derandomised):
-any channel count 1..6 (the vector kernels take 1..4 on 16-byte aligned
-buffers, the others the per-byte kernels), any plane, any k, messages up to
+any channel count 1..6 (unit and vector kernels up to 4 channels, the
+general kernels above), any plane, any k, messages up to
 capacity, buffers at byte offsets 0..15, in place or not, and output
 buffers larger or smaller than the message.  Every byte is compared with
 the oracle, and bytes around the outputs must stay untouched."""

@@ -1,7 +1,7 @@
 """Randomised plain calls (hypothesis, derandomised): raw slices at any t0
 and stream length, header embed/extract of any length up to capacity, every
-k, and buffers at byte offsets 0..15 from aligned allocations (so both the
-vector and the per-byte kernels, and the dword and byte stream paths, run).
+k, and buffers at byte offsets 0..15 from aligned allocations (unaligned
+vector and stream accesses, and streams that start inside a byte).
 Outputs are compared with the oracle byte for byte, and the bytes around
 each output must stay untouched."""
 import numpy as np
