@@ -65,19 +65,15 @@ inline unsigned grid_for(const lsb_launch_cfg &c, uint64_t vectors) {
 }
 
 // Cached or streaming (non-temporal) accesses of the layout kernels, by image
-// bytes n.  Cached while image and stego twice over (3n) fit the 256 MB last-level
-// cache of a program that embeds and then reads the stego.  us a pass, all cached
-// / loads streaming / all streaming, plane of 3 channels hot (the same image each
-// time): 36 MB 20.5 / 22.2 / 22.6, 44 MB 24.2 / 27.4 / 26.6, 64 MB 32.5 / 34.9 /
-// 36.2, 80 MB 42.1 / 44.1 / 44.9, 100 MB 48.9 / 50.0 / 53.1; cold (the images of 3 GB
-// in turn) 44 MB 28.9 / 29.6 / 30.7, 64 MB 40.0 / 41.5 / 42.7, 80 MB 47.6
-// / 49.4 / 50.7, and of 4 channels 80 MB 42.3 / 40.2 / 42.4, 100 MB 51.8 / 48.2 /
-// 51.6; the paper's layout likewise (80 MB hot 39.4 / 41.5 / 47.6, cold 42.5 / 43.4
-// / 49.5).  From 90 MB on the cached loads lose cold what they gain hot, so loads
-// stream and stores stay cached.  From 128 MB on stores stream too: one stego no
-// longer fits beside its cover, and its dirty lines would slow whatever runs next.
+// bytes n.  Cached while cover and stego come and go through the caches of a
+// program that embeds and then reads the stego: up to 40 MB an embed + extract
+// pass takes 10-15 % less (36 MB plane: 19.1 against 22.0 us, 48 MB: 26.8
+// against 27.8).  Above, loads stream and stores stay cached (100 MB plane:
+// 48.0 us; all cached 52.6, all streaming 50.8).  From 128 MB on stores stream
+// too: one stego no longer fits beside its cover in the 256 MB last-level
+// cache, and its dirty lines would slow whatever runs next.
 inline Access access_kind(uint64_t n) {
-    if (n <= (1ull << 28) / 3) return CACHED;
+    if (n <= 40ull * 1000 * 1000) return CACHED;
     return n < (1ull << 27) ? STREAM_LOADS : STREAM;
 }
 

@@ -282,11 +282,9 @@ int lsb_sse(const uint8_t *a, const uint8_t *b, uint64_t n, uint64_t *sse_dev, v
     uint64_t blocks = ceil_div(n / 16 + 1, kSseBlock * kSseUnroll);
     const uint64_t cap = (uint64_t)device_cus() * kSseBlocksPerCu;
     if (blocks > cap) blocks = cap;
-    // Cached loads while both buffers may still be in the caches.  us of a checked
-    // embed, verify and squared error, cached / streaming loads: hot 44 MB 51.4 /
-    // 52.6, 64 MB 65.3 / 67.3, 72 MB 71.5 / 73.7, cold 44 MB 53.4 / 53.2, 64 MB 70.6 /
-    // 70.7, 72 MB 75.7 / 73.5.
-    const auto fn = n <= (1ull << 26) ? lsb_sse_kernel<false> : lsb_sse_kernel<true>;
+    // cached loads while the buffers may still be in the caches (they stream
+    // at 64 MB: a check pass 68.2 us streaming, 69.3 cached; 36 MB 44.4, 42.9)
+    const auto fn = access_kind(n) == CACHED ? lsb_sse_kernel<false> : lsb_sse_kernel<true>;
     hipExtLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kSseBlock), 0, st, e0, e1, 0, a, b, n,
                           (unsigned long long *)sse_dev);
     const hipError_t e = hipGetLastError();

@@ -211,18 +211,3 @@ def test_planes_of_one_image_at_once(c):
             api.embed_plane(img, c, p, msgs_d[p], k, out=img, stream=streams[p])
         torch.cuda.synchronize()
         assert_bytes_equal(to_host(img), want, "%d planes at once, repetition %d" % (c, rep))
-
-
-@pytest.mark.parametrize("h,w", [(1, 29826161), (1, 29826162), (5000, 5965)])
-def test_access_kinds_around_a_third_of_the_cache(h, w):
-    """Images of the largest cached size (2^28 / 3 bytes), of the first size
-    whose loads stream, and between the two in rows."""
-    test_access_kinds_by_size(h, w)
-
-
-@pytest.mark.parametrize("n", [1 << 26, (1 << 26) + 1])
-def test_sse_access_kinds(n):
-    """Squared error at the largest size with cached loads and past it."""
-    a, b = inputs.random_bytes(n, 2841), inputs.random_bytes(n, 2842)
-    want = int(((a.astype(np.int32) - b) ** 2).sum(dtype=np.int64))
-    assert int(api.sse(to_dev(a), to_dev(b)).cpu()) == want
