@@ -65,13 +65,18 @@ inline unsigned grid_for(const lsb_launch_cfg &c, uint64_t vectors) {
 }
 
 // Cached or streaming (non-temporal) accesses of the layout kernels, by image
-// bytes n.  Cached while cover and stego come and go through the caches of a
-// program that embeds and then reads the stego: up to 40 MB an embed + extract
-// pass takes 10-15 % less (36 MB plane: 19.1 against 22.0 us, 48 MB: 26.8
-// against 27.8).  Above, loads stream and stores stay cached (100 MB plane:
-// 48.0 us; all cached 52.6, all streaming 50.8).  From 128 MB on stores stream
-// too: one stego no longer fits beside its cover in the 256 MB last-level
-// cache, and its dirty lines would slow whatever runs next.
+// bytes n.  Cached while three images and their stegos come and go through the
+// caches of a program that embeds and then reads the stego: up to 40 MB an embed +
+// extract pass takes 10-15 % less (36 MB plane: 19.1 against 22.0 us).  Above,
+// loads stream and stores stay cached (100 MB plane: 48.0 us; all cached 52.6, all
+// streaming 50.8).  Cached loads still gain there where one image is embedded into
+// again and again, and lose where images are new, which decides; us a pass, cached
+// / loads streaming, planes of 3 channels, the same image, 3 and 40 images in turn:
+// 48 MB 25.5 / 29.0, 27.7 / 27.0, 29.2 / 28.1; 66 MB at k=6 36.2 / 39.4, 41.9 /
+// 38.0, 42.6 / 39.4; 88 MB 42.7 / 44.9, 48.5 / 44.7, 49.8 / 45.4; the paper's
+// layout 60 MB of 1 channel 33.3 / 34.7, 37.2 / 35.1, 37.9 / 37.8.  From 128 MB
+// on stores stream too: one stego no longer fits beside its cover in the 256 MB
+// last-level cache, and its dirty lines would slow whatever runs next.
 inline Access access_kind(uint64_t n) {
     if (n <= 40ull * 1000 * 1000) return CACHED;
     return n < (1ull << 27) ? STREAM_LOADS : STREAM;

@@ -282,8 +282,9 @@ int lsb_sse(const uint8_t *a, const uint8_t *b, uint64_t n, uint64_t *sse_dev, v
     uint64_t blocks = ceil_div(n / 16 + 1, kSseBlock * kSseUnroll);
     const uint64_t cap = (uint64_t)device_cus() * kSseBlocksPerCu;
     if (blocks > cap) blocks = cap;
-    // cached loads while the buffers may still be in the caches (they stream
-    // at 64 MB: a check pass 68.2 us streaming, 69.3 cached; 36 MB 44.4, 42.9)
+    // cached loads while the buffers may still be in the caches (a checked embed,
+    // verify and squared error in turn, cached / streaming: 36 MB 42.9 / 44.4 us;
+    // images that are new each time 42 MB 49.5 / 48.5, 60 MB 64.0 / 63.5)
     const auto fn = access_kind(n) == CACHED ? lsb_sse_kernel<false> : lsb_sse_kernel<true>;
     hipExtLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kSseBlock), 0, st, e0, e1, 0, a, b, n,
                           (unsigned long long *)sse_dev);
