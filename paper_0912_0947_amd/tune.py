@@ -99,12 +99,13 @@ class Timer:
         torch.cuda.synchronize()
         self.run = {api.OP_EMBED: self._embed, api.OP_EXTRACT: self._extract}
 
-    def use(self, k: int, n: int) -> None:
-        """Covers of n bytes at k, every stego of the arena a valid one."""
+    def use(self, k: int, n: int, at: int = 0) -> None:
+        """Covers of n bytes at k, each ``at`` bytes behind an aligned address,
+        every stego of the arena a valid one."""
         from . import api
 
-        self.k, self.n, self.cap = k, n, min(api.capacity(n, k), 1 << 30)
-        self.step, self.mstep = -(-n // 256) * 256, -(-self.cap // 256) * 256
+        self.k, self.n, self.cap, self.lead = k, n, min(api.capacity(n, k), 1 << 30), at
+        self.step, self.mstep = -(-(at + n) // 256) * 256, -(-self.cap // 256) * 256
         self.slots, self.mslots = self.arena // self.step, self.arena // 4 // self.mstep
         for i in range(self.slots):
             self._embed(i, None)
@@ -112,7 +113,7 @@ class Timer:
     def _embed(self, i, ev):
         from . import api
 
-        c, m = i % self.slots * self.step, i % self.mslots * self.mstep
+        c, m = i % self.slots * self.step + self.lead, i % self.mslots * self.mstep
         if ev:
             self.lib.lsb_time_next_launch(*ev)
         api.embed(self.cover[c:c + self.n], self.msg[m:m + self.cap], self.k, out=self.stego[c:c + self.n])
@@ -120,7 +121,7 @@ class Timer:
     def _extract(self, i, ev):
         from . import api
 
-        c, m = i % self.slots * self.step, i % self.mslots * self.mstep
+        c, m = i % self.slots * self.step + self.lead, i % self.mslots * self.mstep
         if ev:
             self.lib.lsb_time_next_launch(*ev)
         api.extract(self.stego[c:c + self.n], self.k, out=self.out[m:m + self.cap], len_status=self.state)
@@ -230,27 +231,35 @@ def tune_pair(timer: Timer, k: int, n: int, reps: int = 4, finals: int = 24, log
 
 
 def keep_better(timer: Timer, stored, new, rounds: int = 6, log=print):
-    """Of two pairs of entries of one (k, n), the new one only if it is as good
-    in one view and better in the other by more than measurements differ: both
-    pairs take turns, hot and cold; the sum of both views has to fall by 2 %, and
-    neither view may rise by 2 %."""
+    """Of two pairs of entries of one (k, n), the new one only if it is better by
+    more than measurements differ: both pairs take turns, hot and cold, on
+    aligned covers and on covers at byte 54 of a file; the sum of the four views
+    has to fall by 2 %, and none may rise by 2 %.  The covers in a file stand
+    here because they alone show what streaming loads cost when every line is
+    read by two vectors: 50 MB at k=3, extract with such loads 33.3 us a pass
+    against 33.4 us aligned, 40.3 against 37.2 us at byte 54."""
     import statistics
 
     k, n = new[0]["k"], new[0]["n"]
-    times = [([], []) for _ in range(2)]
-    for r in range(rounds + 1):
-        for pair, (hot, cold) in zip((stored, new), times):
-            for e in pair:
-                _install(e["op"], k, n, e["cfg"])
-            h = [sum(p) for p in timer.hot(8)]
-            c = [sum(p) for p in zip(*(timer.cold(e["op"], 8) for e in pair))]
-            if r:
-                hot += h
-                cold += c
-    (h0, c0), (h1, c1) = [[statistics.median(v) for v in views] for views in times]
-    better = h1 + c1 < 0.98 * (h0 + c0) and h1 < 1.02 * h0 and c1 < 1.02 * c0
-    log("k=%d n=%d stored %.2f hot %.2f cold, new %.2f %.2f -> %s" % (k, n, h0, c0, h1, c1,
-                                                                     "new" if better else "stored"))
+    views = [[], []]
+    for at in (0, 54):
+        timer.use(k, n, at)
+        times = [([], []) for _ in range(2)]
+        for r in range(rounds + 1):
+            for pair, (hot, cold) in zip((stored, new), times):
+                for e in pair:
+                    _install(e["op"], k, n, e["cfg"])
+                h = [sum(p) for p in timer.hot(8)]
+                c = [sum(p) for p in zip(*(timer.cold(e["op"], 8) for e in pair))]
+                if r:
+                    hot += h
+                    cold += c
+        for v, both in zip(views, times):
+            v += [statistics.median(t) for t in both]
+    old, got = views
+    better = sum(got) < 0.98 * sum(old) and all(g < 1.02 * o for g, o in zip(got, old))
+    log("k=%d n=%d hot, cold, hot and cold in a file: stored %s us, new %s us -> %s" % (
+        k, n, *(" ".join("%.2f" % t for t in v) for v in views), "new" if better else "stored"))
     for e in new if better else stored:
         _install(e["op"], k, n, e["cfg"])
     return new if better else stored
